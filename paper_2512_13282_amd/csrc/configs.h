@@ -46,7 +46,8 @@ constexpr int32_t kStageKBytes = 128;
 // resident in LDS at once.
 constexpr int32_t kSlotKBytes = 64;
 
-// Family GENERIC: alignment-agnostic element-wise loads (any lda/ldb/K/N).
+// Family GENERIC: operands at any address (any lda/ldb/K/N): 16-byte loads where
+// wide_rows_ok, element by element (configurations 0 and 1 only) otherwise.
 // Family MACRO: 16-byte vector loads staged through registers (B transposed
 // in registers); large tiles.
 // Family SKINNY: same loaders, narrow M tile for M <= 64.
@@ -58,8 +59,8 @@ constexpr int32_t kSlotKBytes = 64;
 // stored column-major, from 16-byte reads like A's.
 constexpr TileConfig kConfigs[] = {
     // family       bm   bn  wm wn occ stages eff_i8 eff_bf16 colB name
-    {FAM_GENERIC,   64,  64, 2, 2, 2, 2, 0.05, 0.07, 1, "generic_64x64_w4"},
-    {FAM_GENERIC,  128, 128, 2, 2, 1, 2, 0.07, 0.10, 1, "generic_128x128_w4"},
+    {FAM_GENERIC,   64,  64, 2, 2, 4, 2, 0.134, 0.145, 1, "generic_64x64_w4"},
+    {FAM_GENERIC,  128, 128, 2, 2, 2, 2, 0.305, 0.272, 1, "generic_128x128_w4"},
     {FAM_MACRO,    256, 256, 2, 2, 1, 2, 0.33, 0.41, 0, "macro_256x256_w4"},
     {FAM_MACRO,    128, 256, 2, 2, 1, 2, 0.27, 0.33, 0, "macro_128x256_w4"},
     {FAM_MACRO,    256, 128, 2, 2, 1, 2, 0.31, 0.33, 0, "macro_256x128_w4"},
@@ -99,6 +100,9 @@ constexpr TileConfig kConfigs[] = {
     {FAM_RING,     256, 128, 2, 2, 2, 3, 0.36, 0.34, 1, "ring_256x128_w4_r3"},
     {FAM_RING,     128, 256, 1, 4, 2, 3, 0.36, 0.34, 1, "ring_128x256_w4c_r3"},
     {FAM_RING,     128, 256, 2, 4, 2, 3, 0.36, 0.34, 1, "ring_128x256_w8_r3"},
+    {FAM_GENERIC,   32, 128, 1, 4, 4, 2, 0.084, 0.143, 1, "generic_32x128_w4"},
+    {FAM_GENERIC,   64, 128, 1, 4, 3, 2, 0.158, 0.227, 1, "generic_64x128_w4"},
+    {FAM_GENERIC,  256, 128, 4, 2, 1, 2, 0.450, 0.379, 1, "generic_256x128_w8"},
 };
 constexpr int32_t kNumConfigs = int32_t(sizeof(kConfigs) / sizeof(kConfigs[0]));
 
@@ -108,6 +112,15 @@ constexpr int32_t kNumConfigs = int32_t(sizeof(kConfigs) / sizeof(kConfigs[0]));
 constexpr int64_t lds_bytes(const TileConfig &c) {
     if (c.family == FAM_GEMV) return c.col_major_b ? 4 * int64_t(c.bn) : 4 * 4 * int64_t(c.bn);
     return int64_t(c.stages) * (int64_t(c.bm) + int64_t(c.bn)) * (c.family == FAM_RING ? kSlotKBytes : kStageKBytes);
+}
+
+// Whether gemm_tile_kernel's 16-byte loads, at any alignment, can read the operands:
+// rows (K of A and of a column-major B, N of a row-major B) of at least 16 bytes, since
+// a row's last piece is read ending at the row's end; and row strides of at most 4 MiB,
+// which keeps a 256-row panel's byte offsets within 32 bits.
+inline bool wide_rows_ok(int32_t dtype, int32_t trans_b, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
+    const int64_t e = dtype == DT_I8 ? 1 : 2, max_row_bytes = int64_t(1) << 22;
+    return K * e >= 16 && (trans_b ? K : N) * e >= 16 && lda * e <= max_row_bytes && ldb * e <= max_row_bytes;
 }
 
 }  // namespace gemm

@@ -28,7 +28,7 @@
 // Families: gemm_lds_kernel (DIRECT: global -> LDS buffer loads into two
 // stages), gemm_ring_kernel (RING: the same loads into a ring of 64-byte
 // slots), gemm_vec_kernel / gemm_tile_kernel (MACRO / GENERIC: loads through
-// registers), gemm_stream_kernel (narrow-M streaming), gemv_kernel and
+// registers; gemm_element_kernel for GENERIC's shortest rows), gemm_stream_kernel (narrow-M streaming), gemv_kernel and
 // gemv_bt_kernel (M = 1 on the vector ALUs), plus the split-K reduction.
 //
 // MFMA fragment layout used (32 x 32 output, 64 lanes): lane l supplies row
@@ -279,21 +279,25 @@ __device__ __forceinline__ void quad_transpose(uint32_t (&x)[4], int lane) {
     x[3] = odd ? z3 : u1;
 }
 
-// Four consecutive outputs of one row as one non-temporal store (16, 8 or 4 bytes).
+// Four consecutive outputs of one row as one non-temporal store (16, 8 or 4 bytes) at
+// any address of the output type: rows of an odd length start anywhere.
+typedef unsigned u32x4_el_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u32x2_el_t __attribute__((ext_vector_type(2), aligned(2)));
+typedef unsigned u32_el_t __attribute__((aligned(1)));
 template <typename O>
 __device__ __forceinline__ void store4_nt(O *dst, const O (&c)[4]) {
     if constexpr (sizeof(O) == 4) {
         const u32x4_t v{__builtin_bit_cast(uint32_t, c[0]), __builtin_bit_cast(uint32_t, c[1]),
                         __builtin_bit_cast(uint32_t, c[2]), __builtin_bit_cast(uint32_t, c[3])};
-        __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t *>(dst));
+        __builtin_nontemporal_store(v, reinterpret_cast<u32x4_el_t *>(dst));
     } else if constexpr (sizeof(O) == 2) {
         const u32x2_t v{uint32_t(__builtin_bit_cast(uint16_t, c[0])) | (uint32_t(__builtin_bit_cast(uint16_t, c[1])) << 16),
                         uint32_t(__builtin_bit_cast(uint16_t, c[2])) | (uint32_t(__builtin_bit_cast(uint16_t, c[3])) << 16)};
-        __builtin_nontemporal_store(v, reinterpret_cast<u32x2_t *>(dst));
+        __builtin_nontemporal_store(v, reinterpret_cast<u32x2_el_t *>(dst));
     } else {
         const uint32_t v = uint32_t(uint8_t(c[0])) | (uint32_t(uint8_t(c[1])) << 8) |
                            (uint32_t(uint8_t(c[2])) << 16) | (uint32_t(uint8_t(c[3])) << 24);
-        __builtin_nontemporal_store(v, reinterpret_cast<uint32_t *>(dst));
+        __builtin_nontemporal_store(v, reinterpret_cast<u32_el_t *>(dst));
     }
 }
 
@@ -307,8 +311,7 @@ __device__ __forceinline__ void store4_nt(O *dst, const O (&c)[4]) {
 // and writes them with one store: a quarter of the store instructions of one
 // element per lane, which is what bounds the epilogue (each wave retires about one
 // store instruction per 80 clocks, whatever its width).  Where the four columns run
-// past N, or C's pitch or address does not allow the wide store, the four values go
-// out one by one.  Row offsets are constants times ldc, which the scalar unit forms.
+// past N, the values left of it go out one by one.  Row offsets are constants times ldc, which the scalar unit forms.
 // The epilogue is a template argument so that the loop bodies stay small enough to
 // unroll fully: the accumulators are then only indexed by constants and stay in
 // registers (with a run-time choice per element, the 256-register tiles of the
@@ -327,7 +330,6 @@ __device__ __forceinline__ void store_c_wide(const KernelArgs &args,
     const int64_t col = c0 + (lane & 28);
     const int64_t rows_left = args.M - row0;
     const int64_t ldc = args.ldc;
-    const bool wide = (ldc % 4) == 0 && (reinterpret_cast<uintptr_t>(args.C) % (4 * sizeof(o_t))) == 0;
     o_t *const base = static_cast<o_t *>(args.C) + row0 * ldc + col;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
@@ -351,7 +353,7 @@ __device__ __forceinline__ void store_c_wide(const KernelArgs &args,
                 const int dr = 32 * i + 8 * g;
                 if (dr < rows_left && cols_left > 0) {
                     o_t *const dst = base + dr * ldc + 32 * j;
-                    if (wide && cols_left >= 4) {
+                    if (cols_left >= 4) {
                         store4_nt(dst, c);
                     } else {
 #pragma unroll

@@ -47,7 +47,8 @@ bool config_applicable(const Problem &p, int32_t cfg) {
     const TileConfig &c = kConfigs[cfg];
     if (p.trans_b && !c.col_major_b) return false;
     if (c.family == FAM_GEMV) return p.M == 1 && (c.col_major_b != 0) == (p.trans_b != 0) && vector_loads_ok(p);
-    if (c.family == FAM_GENERIC) return true;
+    // Configurations 0 and 1 also have an element-wise form for rows too short for 16-byte loads.
+    if (c.family == FAM_GENERIC) return cfg < 2 || wide_rows_ok(p.dtype, p.trans_b, p.N, p.K, p.lda, p.ldb);
     return vector_loads_ok(p);
 }
 
@@ -116,6 +117,19 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     const double eff = p.dtype == DT_I8 ? c.eff_i8 : c.eff_bf16;
     const double wg_s = wg_ops / (cu_rate * eff / c.occupancy);
     pl.t_comp_us = double(rounds) * wg_s * 1e6;
+    double overhead_us = double(rounds) * chip.tile_overhead_us / c.occupancy;
+    // GENERIC: latency-bound loops, so a workgroup speeds up where the last round leaves it
+    // fewer neighbours on its CU, and tiles pay for their outputs (stores of odd rows) more
+    // than for a round.  Fitted on 95 calls of odd sizes (decode, prefill, dense, patches;
+    // every configuration and split timed): the choice runs 1.03x the measured best, the
+    // whole-round model above 1.13x.
+    if (c.family == FAM_GENERIC) {
+        const int64_t full = pl.grid / slots, last = pl.grid % slots;
+        const double resident = last ? double(std::min<int64_t>(c.occupancy, ceil_div(last, chip.cus))) : 0.0;
+        const double units = double(full * c.occupancy) + std::max(resident, last ? chip.generic_solo * c.occupancy : 0.0);
+        pl.t_comp_us = units * wg_s / c.occupancy * 1e6;
+        overhead_us = (double(full * c.occupancy) + resident) * chip.generic_us_per_kilo_output * double(c.bm * c.bn) / 1024.0;
+    }
 
     // Memory: compulsory traffic at HBM speed; tile re-reads (Eqs. 6-7 analog)
     // mostly from L2/MALL; split-K partials written and read back once, or added
@@ -147,8 +161,7 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     // Each round of workgroups also pays its tiles' prologue and epilogue (measured at
     // 2048^3: 1.3 us of first loads and 2.5 us of C stores around an 8.5 us K loop); two
     // workgroups resident on a CU overlap each other's.
-    pl.t_total_us = std::max(pl.t_comp_us, pl.t_mem_us) + double(rounds) * chip.tile_overhead_us / c.occupancy +
-                    chip.launch_us + red_us;
+    pl.t_total_us = std::max(pl.t_comp_us, pl.t_mem_us) + overhead_us + chip.launch_us + red_us;
     return pl;
 }
 
