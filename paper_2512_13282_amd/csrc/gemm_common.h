@@ -279,25 +279,35 @@ __device__ __forceinline__ void quad_transpose(uint32_t (&x)[4], int lane) {
     x[3] = odd ? z3 : u1;
 }
 
-// Four consecutive outputs of one row as one non-temporal store (16, 8 or 4 bytes) at
-// any address of the output type: rows of an odd length start anywhere.
+// One output, non-temporal (NT) or through the L2.
+template <bool NT, typename O>
+__device__ __forceinline__ void store_out(O *dst, O v) {
+    if constexpr (NT) __builtin_nontemporal_store(v, dst);
+    else *dst = v;
+}
+
+// Four consecutive outputs of one row as one store (16, 8 or 4 bytes) at any address of
+// the output type: rows of an odd length start anywhere.
 typedef unsigned u32x4_el_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned u32x2_el_t __attribute__((ext_vector_type(2), aligned(2)));
 typedef unsigned u32_el_t __attribute__((aligned(1)));
-template <typename O>
-__device__ __forceinline__ void store4_nt(O *dst, const O (&c)[4]) {
+template <bool NT, typename O>
+__device__ __forceinline__ void store4(O *dst, const O (&c)[4]) {
     if constexpr (sizeof(O) == 4) {
         const u32x4_t v{__builtin_bit_cast(uint32_t, c[0]), __builtin_bit_cast(uint32_t, c[1]),
                         __builtin_bit_cast(uint32_t, c[2]), __builtin_bit_cast(uint32_t, c[3])};
-        __builtin_nontemporal_store(v, reinterpret_cast<u32x4_el_t *>(dst));
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_el_t *>(dst));
+        else *reinterpret_cast<u32x4_el_t *>(dst) = v;
     } else if constexpr (sizeof(O) == 2) {
         const u32x2_t v{uint32_t(__builtin_bit_cast(uint16_t, c[0])) | (uint32_t(__builtin_bit_cast(uint16_t, c[1])) << 16),
                         uint32_t(__builtin_bit_cast(uint16_t, c[2])) | (uint32_t(__builtin_bit_cast(uint16_t, c[3])) << 16)};
-        __builtin_nontemporal_store(v, reinterpret_cast<u32x2_el_t *>(dst));
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<u32x2_el_t *>(dst));
+        else *reinterpret_cast<u32x2_el_t *>(dst) = v;
     } else {
         const uint32_t v = uint32_t(uint8_t(c[0])) | (uint32_t(uint8_t(c[1])) << 8) |
                            (uint32_t(uint8_t(c[2])) << 16) | (uint32_t(uint8_t(c[3])) << 24);
-        __builtin_nontemporal_store(v, reinterpret_cast<u32_el_t *>(dst));
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<u32_el_t *>(dst));
+        else *reinterpret_cast<u32_el_t *>(dst) = v;
     }
 }
 
@@ -320,7 +330,7 @@ __device__ __forceinline__ void store4_nt(O *dst, const O (&c)[4]) {
 // keeps the A and B panels that other workgroups are still reading resident in L2
 // and in the last-level cache (measured at 8192^3: 6 % faster for int8, 3 % for
 // bf16).
-template <int DT, int EPI, int TM, int TN>
+template <int DT, int EPI, bool NT, int TM, int TN>
 __device__ __forceinline__ void store_c_wide(const KernelArgs &args,
                                                const typename Types<DT>::acc_vec (&acc)[TM][TN],
                                                int64_t r0, int64_t c0, int lane) {
@@ -354,11 +364,11 @@ __device__ __forceinline__ void store_c_wide(const KernelArgs &args,
                 if (dr < rows_left && cols_left > 0) {
                     o_t *const dst = base + dr * ldc + 32 * j;
                     if (cols_left >= 4) {
-                        store4_nt(dst, c);
+                        store4<NT>(dst, c);
                     } else {
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
-                            if (k < cols_left) __builtin_nontemporal_store(c[k], dst + k);
+                            if (k < cols_left) store_out<NT>(dst + k, c[k]);
                     }
                 }
             }
@@ -373,7 +383,7 @@ __device__ __forceinline__ void store_c_wide(const KernelArgs &args,
 // c0 + l % 32 + 32 j, two rows per store instruction).  Kept for the 4-wave
 // 256 x 256 tiles, whose waves each hold a 128 x 128 block (256 accumulator
 // registers): the transposes' extra live values would push them into scratch.
-template <int DT, int EPI, int TM, int TN>
+template <int DT, int EPI, bool NT, int TM, int TN>
 __device__ __forceinline__ void store_c_elementwise(const KernelArgs &args,
                                                     const typename Types<DT>::acc_vec (&acc)[TM][TN],
                                                     int64_t r0, int64_t c0, int lane) {
@@ -392,7 +402,7 @@ __device__ __forceinline__ void store_c_elementwise(const KernelArgs &args,
             for (int r = 0; r < 16; ++r) {
                 const int dr = 32 * i + 8 * (r >> 2) + (r & 3);
                 if (dr < rows_left)
-                    __builtin_nontemporal_store(convert_out<DT, EPI>(args, acc[i][j][r]), &base[dr * ldc + 32 * j]);
+                    store_out<NT>(&base[dr * ldc + 32 * j], convert_out<DT, EPI>(args, acc[i][j][r]));
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -404,12 +414,27 @@ __device__ __forceinline__ void store_c_elementwise(const KernelArgs &args,
 // store instructions and gain (128 x 128 at 2048^3: 3.5 %); tiles of eight waves
 // lose 1-7 %, their epilogue being bound by the chip's aggregate write rate rather
 // than by store instructions, so the transposes only add VALU work.
+//
+// Non-temporal stores only where every row of C starts on a 128-byte line: elsewhere a
+// fragment's piece of a row ends inside lines that the next fragment, wave or tile
+// continues, and streaming the parts past the L2 writes each such line to memory more
+// than once.  Through the L2 the parts meet (fp32 4904 x 7397 x 159: 124 -> 52 us at
+// 128 x 128 tiles; 868 x 6995 x 1089: 40 -> 32 us; bf16 256 x 32003 x 4096: 98 -> 86 us);
+// with whole lines the non-temporal form is the faster one (fp32 4904 x 7424 x 159: 45.7
+// against 47.6 us; int32 50176 x 64 x 147: 6.7 against 7.9 us).
 template <int DT, int EPI, int WAVES, int TM, int TN>
 __device__ __forceinline__ void store_c_direct(const KernelArgs &args,
                                                const typename Types<DT>::acc_vec (&acc)[TM][TN],
                                                int64_t r0, int64_t c0, int lane) {
-    if constexpr (WAVES <= 4 && TM * TN <= 4) store_c_wide<DT, EPI, TM, TN>(args, acc, r0, c0, lane);
-    else store_c_elementwise<DT, EPI, TM, TN>(args, acc, r0, c0, lane);
+    constexpr bool WIDE = WAVES <= 4 && TM * TN <= 4;
+    constexpr int64_t LINE = 128 / int64_t(sizeof(typename OutElem<DT, EPI>::type));
+    if (args.ldc % LINE == 0 && reinterpret_cast<uintptr_t>(args.C) % 128 == 0) {
+        if constexpr (WIDE) store_c_wide<DT, EPI, true>(args, acc, r0, c0, lane);
+        else store_c_elementwise<DT, EPI, true>(args, acc, r0, c0, lane);
+    } else {
+        if constexpr (WIDE) store_c_wide<DT, EPI, false>(args, acc, r0, c0, lane);
+        else store_c_elementwise<DT, EPI, false>(args, acc, r0, c0, lane);
+    }
 }
 
 // s_last: one int of LDS for the in-kernel split-K reduction's "last slice"
