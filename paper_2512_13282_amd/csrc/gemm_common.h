@@ -203,14 +203,16 @@ __device__ __forceinline__ void flag_take_credit(const KernelArgs &args, int til
 // Output element idx (row * ldc + col, in output elements) of C from a result v of
 // the accumulator type, converted as the call's epilogue asks (launch.h).  int32
 // partial sums arrive as uint32 (they wrap modulo 2^32) and are read back as int32.
+//
+// The division by 2^shift stays in 32 bits: with q = floor(v / 2^shift) and the remainder
+// r in [0, 2^shift), the nearest integer (ties to even) is q + 1 exactly where r plus q's
+// low bit exceeds half, 2^(shift - 1); at shift 0 the half is set past any remainder.
+// Neither sum can wrap (r < 2^31, and q <= 2^30 wherever it is stepped).
 __device__ __forceinline__ int32_t requant_nearest_even(int32_t v, int shift, int32_t lo, int32_t hi) {
-    const int64_t x = v;
-    int64_t q = x >> shift;                              // floor(x / 2^shift)
-    if (shift > 0) {
-        const int64_t r = x - (q << shift), half = int64_t(1) << (shift - 1);
-        if (r > half || (r == half && (q & 1))) ++q;
-    }
-    return int32_t(q < lo ? lo : (q > hi ? hi : q));
+    const int32_t q = v >> shift;
+    const uint32_t mask = (1u << shift) - 1u, half = shift > 0 ? 1u << (shift - 1) : 2u;
+    const int32_t n = q + (((uint32_t(v) & mask) + (uint32_t(q) & 1u)) > half ? 1 : 0);
+    return n < lo ? lo : (n > hi ? hi : n);
 }
 
 // fp32 -> bf16, round to nearest with ties to even.  A NaN keeps its upper half with
