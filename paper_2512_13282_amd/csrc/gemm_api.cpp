@@ -37,10 +37,10 @@ Override g_override[2];
 struct Key {
     int32_t dtype;
     int64_t M, N, K;
-    bool vec;
+    int32_t align;     // alignment_class
     int32_t trans_b;
     bool operator==(const Key &o) const {
-        return dtype == o.dtype && M == o.M && N == o.N && K == o.K && vec == o.vec && trans_b == o.trans_b;
+        return dtype == o.dtype && M == o.M && N == o.N && K == o.K && align == o.align && trans_b == o.trans_b;
     }
 };
 // 64-bit FNV-1a over the key's fields (its published offset basis and prime).
@@ -49,7 +49,7 @@ struct KeyHash {
         uint64_t h = 1469598103934665603ULL;
         auto mix = [&](uint64_t v) { h = (h ^ v) * 1099511628211ULL; };
         mix(uint64_t(k.dtype)); mix(uint64_t(k.M)); mix(uint64_t(k.N)); mix(uint64_t(k.K));
-        mix(uint64_t(k.vec)); mix(uint64_t(k.trans_b));
+        mix(uint64_t(k.align)); mix(uint64_t(k.trans_b));
         return size_t(h);
     }
 };
@@ -70,7 +70,7 @@ struct Shape {
     }
 };
 struct ShapeHash {
-    size_t operator()(const Shape &s) const { return KeyHash()(Key{s.dtype, s.M, s.N, s.K, false, s.trans_b}); }
+    size_t operator()(const Shape &s) const { return KeyHash()(Key{s.dtype, s.M, s.N, s.K, 0, s.trans_b}); }
 };
 struct LoadedPlan {
     int32_t config, split, reduce;
@@ -191,7 +191,7 @@ int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr) {
     }
     const bool forced = ov.family >= 0 || ov.config >= 0 || ov.split > 0 || ov.reduce >= 0;
     if (!forced) {
-        const Key key{p.dtype, p.M, p.N, p.K, gemm::vector_loads_ok(p), p.trans_b};
+        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b};
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_cache.find(key);
         if (it != g_cache.end()) {
@@ -224,7 +224,7 @@ int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr) {
                       : gemm::neighbour_plan(p, &cfg, &split, &reduce) ? GEMM_PLAN_FROM_NEIGHBOUR
                       : GEMM_PLAN_FROM_MODEL;
     if (!forced) {
-        const Key key{p.dtype, p.M, p.N, p.K, gemm::vector_loads_ok(p), p.trans_b};
+        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b};
         std::lock_guard<std::mutex> lk(g_mu);
         if (g_cache.size() > 4096) g_cache.clear();
         g_cache.emplace(key, CachedPlan{pl, src});

@@ -353,3 +353,16 @@ def test_memory_bound_ties_go_to_the_faster_kernel(dtype):
                 assert q["model_t_comp_us"] >= p["model_t_comp_us"] - 1e-9, (q["name"], p["name"])
     finally:
         b.gemm_force_plan(dtype, b.GEMM_KERNEL_AUTO, -1, 0)
+
+
+@pytest.mark.parametrize("dtype", [I8, BF])
+def test_cached_plans_follow_strides(dtype):
+    """A plan cached for one call is not used for another of the same sizes whose strides it
+    cannot run: row strides past 4 MiB take the element-wise kernels' configurations."""
+    M, N, K = 40, 700, 333
+    near = b.gemm_plan(dtype, M, N, K, K, N, N, AL, 2 * AL, 3 * AL)
+    far = b.gemm_plan(dtype, M, N, K, (1 << 23), N, N, AL, 2 * AL, 3 * AL)
+    assert far["config"] in (0, 1) and far["kernel"] == b.GEMM_KERNEL_GENERIC
+    assert b.gemm_plan(dtype, M, N, K, K, N, N, AL, 2 * AL, 3 * AL) == near
+    check_invariants(near, dtype, M, N, K)
+    check_invariants(far, dtype, M, N, K)
