@@ -56,7 +56,8 @@ constexpr int32_t kSlotKBytes = 64;
 // vector-ALU multiply-add rate as a fraction of the MFMA peak.
 // Family DIRECT: both operands stream global -> LDS directly (buffer loads with
 // an LDS destination); B's fragments come from LDS transpose reads, or, for B
-// stored column-major, from 16-byte reads like A's.
+// stored column-major, from 16-byte reads like A's.  The ping-pong kernel has two rows:
+// 13, row-major B only (plan files name configurations by index), and 44, both layouts.
 constexpr TileConfig kConfigs[] = {
     // family       bm   bn  wm wn occ stages eff_i8 eff_bf16 colB name
     {FAM_GENERIC,   64,  64, 2, 2, 4, 2, 0.134, 0.145, 1, "generic_64x64_w4"},
@@ -72,7 +73,7 @@ constexpr TileConfig kConfigs[] = {
     {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.44, 0.51, 1, "direct_256x256_w8"},
     {FAM_DIRECT,   256, 256, 4, 2, 1, 2, 0.45, 0.51, 1, "direct_256x256_w8t"},
     {FAM_DIRECT,   128, 256, 2, 4, 1, 2, 0.42, 0.36, 1, "direct_128x256_w8"},
-    {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.30, 0.30, 0, "pingpong_256x256_w8"},
+    {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.49, 0.55, 0, "pingpong_256x256_w8"},
     {FAM_SKINNY,    32, 256, 1, 4, 1, 4, 0.10, 0.12, 0, "stream_32x256_s4"},
     {FAM_SKINNY,    64, 256, 1, 4, 1, 3, 0.15, 0.18, 0, "stream_64x256_s3"},
     {FAM_RING,     256, 256, 2, 4, 1, 4, 0.40, 0.45, 1, "ring_256x256_w8"},
@@ -103,6 +104,7 @@ constexpr TileConfig kConfigs[] = {
     {FAM_GENERIC,   32, 128, 1, 4, 4, 2, 0.084, 0.143, 1, "generic_32x128_w4"},
     {FAM_GENERIC,   64, 128, 1, 4, 3, 2, 0.158, 0.227, 1, "generic_64x128_w4"},
     {FAM_GENERIC,  256, 128, 4, 2, 1, 2, 0.450, 0.379, 1, "generic_256x128_w8"},
+    {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.50, 0.56, 1, "quad_256x256_w8"},
 };
 constexpr int32_t kNumConfigs = int32_t(sizeof(kConfigs) / sizeof(kConfigs[0]));
 

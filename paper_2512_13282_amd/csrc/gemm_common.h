@@ -332,7 +332,7 @@ __device__ __forceinline__ void store4(O *dst, const O (&c)[4]) {
 // keeps the A and B panels that other workgroups are still reading resident in L2
 // and in the last-level cache (measured at 8192^3: 6 % faster for int8, 3 % for
 // bf16).
-template <int DT, int EPI, bool NT, int TM, int TN>
+template <int DT, int EPI, bool NT, int CS, int TM, int TN>
 __device__ __forceinline__ void store_c_wide(const KernelArgs &args,
                                                const typename Types<DT>::acc_vec (&acc)[TM][TN],
                                                int64_t r0, int64_t c0, int lane) {
@@ -345,7 +345,7 @@ __device__ __forceinline__ void store_c_wide(const KernelArgs &args,
     o_t *const base = static_cast<o_t *>(args.C) + row0 * ldc + col;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        const int64_t cols_left = args.N - (col + 32 * j);
+        const int64_t cols_left = args.N - (col + CS * j);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -364,7 +364,7 @@ __device__ __forceinline__ void store_c_wide(const KernelArgs &args,
                 for (int k = 0; k < 4; ++k) c[k] = convert_out<DT, EPI>(args, __builtin_bit_cast(out_t, x[k]));
                 const int dr = 32 * i + 8 * g;
                 if (dr < rows_left && cols_left > 0) {
-                    o_t *const dst = base + dr * ldc + 32 * j;
+                    o_t *const dst = base + dr * ldc + CS * j;
                     if (cols_left >= 4) {
                         store4<NT>(dst, c);
                     } else {
@@ -385,7 +385,7 @@ __device__ __forceinline__ void store_c_wide(const KernelArgs &args,
 // c0 + l % 32 + 32 j, two rows per store instruction).  Kept for the 4-wave
 // 256 x 256 tiles, whose waves each hold a 128 x 128 block (256 accumulator
 // registers): the transposes' extra live values would push them into scratch.
-template <int DT, int EPI, bool NT, int TM, int TN>
+template <int DT, int EPI, bool NT, int CS, int TM, int TN>
 __device__ __forceinline__ void store_c_elementwise(const KernelArgs &args,
                                                     const typename Types<DT>::acc_vec (&acc)[TM][TN],
                                                     int64_t r0, int64_t c0, int lane) {
@@ -397,14 +397,14 @@ __device__ __forceinline__ void store_c_elementwise(const KernelArgs &args,
     o_t *const base = static_cast<o_t *>(args.C) + row0 * ldc + col;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        if (col + 32 * j >= args.N) continue;
+        if (col + CS * j >= args.N) continue;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int dr = 32 * i + 8 * (r >> 2) + (r & 3);
                 if (dr < rows_left)
-                    store_out<NT>(&base[dr * ldc + 32 * j], convert_out<DT, EPI>(args, acc[i][j][r]));
+                    store_out<NT>(&base[dr * ldc + CS * j], convert_out<DT, EPI>(args, acc[i][j][r]));
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -424,26 +424,27 @@ __device__ __forceinline__ void store_c_elementwise(const KernelArgs &args,
 // 128 x 128 tiles; 868 x 6995 x 1089: 40 -> 32 us; bf16 256 x 32003 x 4096: 98 -> 86 us);
 // with whole lines the non-temporal form is the faster one (fp32 4904 x 7424 x 159: 45.7
 // against 47.6 us; int32 50176 x 64 x 147: 6.7 against 7.9 us).
-template <int DT, int EPI, int WAVES, int TM, int TN>
+template <int DT, int EPI, int WAVES, int CS, int TM, int TN>
 __device__ __forceinline__ void store_c_direct(const KernelArgs &args,
                                                const typename Types<DT>::acc_vec (&acc)[TM][TN],
                                                int64_t r0, int64_t c0, int lane) {
     constexpr bool WIDE = WAVES <= 4 && TM * TN <= 4;
     constexpr int64_t LINE = 128 / int64_t(sizeof(typename OutElem<DT, EPI>::type));
     if (args.ldc % LINE == 0 && reinterpret_cast<uintptr_t>(args.C) % 128 == 0) {
-        if constexpr (WIDE) store_c_wide<DT, EPI, true>(args, acc, r0, c0, lane);
-        else store_c_elementwise<DT, EPI, true>(args, acc, r0, c0, lane);
+        if constexpr (WIDE) store_c_wide<DT, EPI, true, CS>(args, acc, r0, c0, lane);
+        else store_c_elementwise<DT, EPI, true, CS>(args, acc, r0, c0, lane);
     } else {
-        if constexpr (WIDE) store_c_wide<DT, EPI, false>(args, acc, r0, c0, lane);
-        else store_c_elementwise<DT, EPI, false>(args, acc, r0, c0, lane);
+        if constexpr (WIDE) store_c_wide<DT, EPI, false, CS>(args, acc, r0, c0, lane);
+        else store_c_elementwise<DT, EPI, false, CS>(args, acc, r0, c0, lane);
     }
 }
 
+// CS: columns from a wave's fragment j to j + 1.
 // s_last: one int of LDS for the in-kernel split-K reduction's "last slice"
 // broadcast; a kernel whose LDS is otherwise free at this point may lend it a word
 // of its operand buffers (all of its global -> LDS loads complete, all of its
 // fragment reads done).
-template <int DT, int BM, int BN, int TM, int TN>
+template <int DT, int BM, int BN, int TM, int TN, int CS = 32>
 __device__ __forceinline__ void store_tile(const KernelArgs &args,
                                            const typename Types<DT>::acc_vec (&acc)[TM][TN],
                                            int tm, int tn, int slice, int64_t r0, int64_t c0, int lane,
@@ -457,12 +458,12 @@ __device__ __forceinline__ void store_tile(const KernelArgs &args,
     if (args.split_k == 1) {
         // C itself, through the call's output conversion.
         if constexpr (DT == DT_I8) {
-            if (args.epilogue == EPI_I8) store_c_direct<DT, EPI_I8, WAVES>(args, acc, r0, c0, lane);
-            else if (args.epilogue == EPI_I16) store_c_direct<DT, EPI_I16, WAVES>(args, acc, r0, c0, lane);
-            else store_c_direct<DT, EPI_NONE, WAVES>(args, acc, r0, c0, lane);
+            if (args.epilogue == EPI_I8) store_c_direct<DT, EPI_I8, WAVES, CS>(args, acc, r0, c0, lane);
+            else if (args.epilogue == EPI_I16) store_c_direct<DT, EPI_I16, WAVES, CS>(args, acc, r0, c0, lane);
+            else store_c_direct<DT, EPI_NONE, WAVES, CS>(args, acc, r0, c0, lane);
         } else {
-            if (args.epilogue == EPI_BF16) store_c_direct<DT, EPI_BF16, WAVES>(args, acc, r0, c0, lane);
-            else store_c_direct<DT, EPI_NONE, WAVES>(args, acc, r0, c0, lane);
+            if (args.epilogue == EPI_BF16) store_c_direct<DT, EPI_BF16, WAVES, CS>(args, acc, r0, c0, lane);
+            else store_c_direct<DT, EPI_NONE, WAVES, CS>(args, acc, r0, c0, lane);
         }
         return;
     }
@@ -477,7 +478,7 @@ __device__ __forceinline__ void store_tile(const KernelArgs &args,
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    const int64_t col = c0 + j * 32 + frag_row;
+                    const int64_t col = c0 + j * CS + frag_row;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int64_t row = r0 + i * 32 + 8 * (r >> 2) + 4 * frag_half + (r & 3);
@@ -496,7 +497,7 @@ __device__ __forceinline__ void store_tile(const KernelArgs &args,
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const int64_t col = c0 + j * 32 + frag_row;
+                const int64_t col = c0 + j * CS + frag_row;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int64_t row = r0 + i * 32 + 8 * (r >> 2) + 4 * frag_half + (r & 3);
@@ -513,7 +514,7 @@ __device__ __forceinline__ void store_tile(const KernelArgs &args,
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const int64_t col = c0 + j * 32 + frag_row;
+                const int64_t col = c0 + j * CS + frag_row;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int64_t row = r0 + i * 32 + 8 * (r >> 2) + 4 * frag_half + (r & 3);

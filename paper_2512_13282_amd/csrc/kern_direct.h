@@ -1,5 +1,5 @@
-// kern_direct.h -- direct-to-LDS kernels: DIRECT (two 128-byte K stages) and
-// the ping-pong variant.
+// kern_direct.h -- direct-to-LDS kernels with two 128-byte K stages: all waves in
+// step (gemm_lds_kernel) and two wave groups in turn (gemm_pingpong_kernel).
 #pragma once
 
 #include "gemm_common.h"
@@ -310,50 +310,62 @@ void gemm_lds_kernel(KernelArgs args) {
 }
 
 // ---------------------------------------------------------------------------
-// Ping-pong direct-to-LDS kernel: 256 x 256 macro-tile, 8 waves, two wave
-// groups that alternate between a compute phase and a memory phase.
+// Ping-pong kernel: 256 x 256 macro-tile, 8 waves, two wave groups that alternate
+// between reading fragments and running MFMAs.
 //
-// Waves w and w + 4 share a SIMD.  Group 0 (waves 0-3) owns output rows 0-127
-// of the tile, group 1 rows 128-255; each wave a 128 x 64 sub-tile.  A "unit"
-// is half a stage (two MFMA k-steps).  Group 1 runs one phase behind group 0,
-// so in every phase one wave per SIMD issues a dense run of 16 MFMAs from
-// fragments already in registers while the other reads its next unit's
-// fragments from LDS and issues its share of the next stage's global -> LDS
-// loads.  Phases are separated by workgroup barriers.  Stage s sits in LDS
-// buffer s % 2 and is read in phases 4s .. 4s+3; the loads of stage s+1 are
-// issued in phases 4s (group 0) and 4s+1 (group 1) and waited for at the end
-// of phase 4s+3, so a load has three phases to land.  Every wave executes
-// the same barrier sequence; only the work between barriers depends on the
-// group.
+// Waves w and w + 4 share a SIMD; group 0 is waves 0-3, group 1 waves 4-7.  Every
+// wave owns a 128 x 64 block of C as four quadrants, 64 rows x 32 columns each.  A
+// stage (128 K-bytes) sits in LDS as four units of 16 KiB: A0, A1 (128 rows each: the
+// first and second 64 rows of both wave rows) and B0, B1 (columns 0-127 and 128-255).
+// A phase is one quadrant over the whole stage: read one unit's fragments, issue two
+// loads, barrier, eight MFMAs, barrier:
+//   phase 1: read A0, MFMA A0 x B0, load B0 two stages ahead
+//   phase 2: read B1, MFMA A0 x B1, load A0 two stages ahead
+//   phase 3: read A1, MFMA A1 x B0, load B1 two stages ahead
+//   phase 4: read B0 of the next stage, MFMA A1 x B1, load A1 two stages ahead
+// Group 1 runs one barrier behind, so between any two barriers one wave of each SIMD
+// runs MFMAs from registers while the other reads and loads; neither waits for the
+// other's LDS latency.
+//
+// Why units and quadrants: a unit is free as soon as both groups have read it, a phase
+// after its own, so its successor's loads leave six phases (about 3000 clocks) before
+// the wait for them with only two stages of LDS, and every load still takes whole
+// 128-byte row pieces.  gemm_lds_kernel waits at the end of each stage for loads issued
+// at its beginning, too late for the fifth of them that miss L2; gemm_ring_kernel leads
+// as far, but in 64-byte pieces, which cost the L2 twice the lines.
+//
+// Order of every access to a unit: loads into it are waited for (vmcnt) by the wave
+// that issued them before the barrier that ends its fragment reads of the phase before
+// the unit is read, by both groups; reads of it complete (lgkmcnt) before the barrier
+// that ends them; and the next loads into it are issued after both groups' barriers.
+// Stages past the end of K load zeros through an empty resource, so that every phase
+// issues the same two loads and the wait is a fixed count (12: six phases' loads).
+//
+// Measured against gemm_lds_kernel at the same tile: 8192^3 bf16 835 -> 771 us (1426
+// TFLOP/s), column-major B 845 -> 779; int8 437 -> 421 us (2610 TOPS), column-major 429
+// -> 415.  What bounds it now: MFMAs at the clock the power limit leaves (1.5-1.65 GHz).
 // ---------------------------------------------------------------------------
-template <int DT>
+template <int DT, bool BT>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
 void gemm_pingpong_kernel(KernelArgs args) {
     using acc_vec = typename Types<DT>::acc_vec;
-    using out_t = typename Types<DT>::out_t;
-    constexpr int BM = 256, BN = 256, WAVES = 8;
+    constexpr int BM = 256, BN = 256, HALF = 128, WAVES = 8;
     constexpr int E = Types<DT>::E;
     constexpr int VECE = 16 / E;
     constexpr int BK = kStageKBytes / E;
-    constexpr int TM = 4, TN = 2;                          // 128 x 64 per wave
-    constexpr int A_STAGE = BM * kStageKBytes;
-    constexpr int B_PITCH = BN * E;
-    constexpr int B_STAGE = BK * B_PITCH;
-    constexpr int A_INSTR = A_STAGE / 1024 / WAVES;        // 4
-    constexpr int B_INSTR = B_STAGE / 1024 / WAVES;        // 4
-    constexpr int B_ROWS_PER_KB = 1024 / B_PITCH;
-    constexpr int B_CPR = B_PITCH / 16;
+    constexpr int TM = 4, TN = 2;
+    constexpr int UNIT = HALF * kStageKBytes;              // 16 KiB
+    constexpr int B_PITCH = BT ? kStageKBytes : HALF * E;  // bytes per B row in LDS
+    constexpr int B_CPR = B_PITCH / 16;                    // 16-byte chunks per B row
+    enum { U_B0, U_A0, U_B1, U_A1 };                       // units of a stage, in load order
 
-    __shared__ __attribute__((aligned(1024))) uint8_t a_lds0[A_STAGE];
-    __shared__ __attribute__((aligned(1024))) uint8_t a_lds1[A_STAGE];
-    __shared__ __attribute__((aligned(1024))) uint8_t b_lds0[B_STAGE];
-    __shared__ __attribute__((aligned(1024))) uint8_t b_lds1[B_STAGE];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[2][4][UNIT];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int grp = wave >> 2;
-    const int wave_m = grp, wave_n = wave & 3;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = wave >> 2;                             // also the wave's row of the tile
+    const int wave_n = wave & 3;
 
     int tm, tn, slice;
     map_tile(args, tm, tn, slice);
@@ -362,100 +374,108 @@ void gemm_pingpong_kernel(KernelArgs args) {
     const int64_t k_begin = int64_t(slice) * args.k_chunk;
     int64_t k_end = k_begin + args.k_chunk;
     if (k_end > args.K) k_end = args.K;
-    const int nk = k_end > k_begin ? int((k_end - k_begin + BK - 1) / BK) : 0;
+    const int k_len = k_end > k_begin ? int(k_end - k_begin) : 0;
+    const int ns = (k_len + BK - 1) / BK;
     const int64_t lda_b = args.lda * E, ldb_b = args.ldb * E;
 
-    // global -> LDS source offsets (see gemm_lds_kernel)
+    // ---- global source offsets of this lane's pieces: load i of unit h fills unit bytes
+    // [(8 i + wave) KiB, + 1 KiB) ----
     const int64_t a_rows_valid = (M - m0) < BM ? (M - m0) : BM;
     const uint32_t a_bytes = uint32_t(a_rows_valid * lda_b);
-    uint32_t a_voff[A_INSTR];
-    int a_chunk[A_INSTR];
+    const int64_t b_rows_valid = (N - n0) < BN ? (N - n0) : BN;
+    const uint32_t bt_bytes = uint32_t(b_rows_valid * ldb_b);
+    uint32_t a_voff[2][2], b_voff[2][2];
+    int a_chunk[2], b_chunk[2];
 #pragma unroll
-    for (int i = 0; i < A_INSTR; ++i) {
+    for (int i = 0; i < 2; ++i) {
         const int row = (i * WAVES + wave) * 8 + (lane >> 3);
-        const int c = (lane & 7) ^ ((row ^ (row >> 3)) & 7);
+        const int c = swz(lane & 7, row);
         a_chunk[i] = c;
-        a_voff[i] = uint32_t(row * lda_b + c * 16);
-    }
-    uint32_t b_voff[B_INSTR];
+        // unit row r of A_h: tile row (r / 64) * 128 + h * 64 + r % 64
 #pragma unroll
-    for (int i = 0; i < B_INSTR; ++i) {
-        const int row = (i * WAVES + wave) * B_ROWS_PER_KB + lane / B_CPR;
-        const int c = (lane % B_CPR) ^ bswz<DT>(row);
-        b_voff[i] = (n0 + int64_t(c) * VECE < N) ? uint32_t(row * ldb_b + c * 16) : kOOB;
+        for (int h = 0; h < 2; ++h)
+            a_voff[h][i] = uint32_t(((row >> 6) * 128 + h * 64 + (row & 63)) * lda_b + c * 16);
+        if constexpr (BT) {
+            b_chunk[i] = c;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) b_voff[h][i] = uint32_t((h * HALF + row) * ldb_b + c * 16);
+        } else {
+            const int k = (i * WAVES + wave) * (1024 / B_PITCH) + lane / B_CPR;
+            const int cb = (lane % B_CPR) ^ ring_bswz<DT, B_CPR>(k);
+            b_chunk[i] = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                b_voff[h][i] = n0 + h * HALF + cb * VECE < N ? uint32_t(k * ldb_b + h * HALF * E + cb * 16) : kOOB;
+        }
     }
     const uint8_t *const a_base = static_cast<const uint8_t *>(args.A) + (m0 * args.lda + k_begin) * E;
-    const uint8_t *const b_base = static_cast<const uint8_t *>(args.B) + (k_begin * args.ldb + n0) * E;
-    const int64_t k_len = k_end - k_begin;
+    const uint8_t *const b_base = static_cast<const uint8_t *>(args.B) +
+                                  (BT ? n0 * args.ldb + k_begin : k_begin * args.ldb + n0) * E;
 
-    auto load_stage = [&](int kt, auto buf_c) {
-        constexpr int BUF = decltype(buf_c)::value;
-        const int64_t rem = k_len - int64_t(kt) * BK;
-        const __amdgpu_buffer_rsrc_t ra = make_rsrc(a_base + int64_t(kt) * kStageKBytes, a_bytes);
-        const int64_t rows = rem <= 0 ? 0 : (rem < BK ? rem : BK);
-        const __amdgpu_buffer_rsrc_t rb = make_rsrc(b_base + int64_t(kt) * BK * ldb_b, uint32_t(rows * ldb_b));
-        uint8_t *const as = BUF ? a_lds1 : a_lds0;
-        uint8_t *const bs = BUF ? b_lds1 : b_lds0;
-        if (rem >= BK) {
+    // Issues this wave's two loads of unit U of stage kt (buffer BUF).
+    auto load_unit = [&](int kt, auto buf_c, auto u_c) {
+        constexpr int BUF = decltype(buf_c)::value, U = decltype(u_c)::value;
+        const int rem = k_len - kt * BK;
+        const uint32_t dst = lds_addr(lds[BUF][U]) + uint32_t(wave) * 1024u;
+        if constexpr (U == U_A0 || U == U_A1) {
+            const i32x4_t r = ring_rsrc(a_base + int64_t(kt) * kStageKBytes, rem > 0 ? a_bytes : 0u);
 #pragma unroll
-            for (int i = 0; i < A_INSTR; ++i) {
-                load_lds16(ra, as + (i * WAVES + wave) * 1024, a_voff[i]);
-                load_lds16(rb, bs + (i * WAVES + wave) * 1024, b_voff[i]);
-            }
+            for (int i = 0; i < 2; ++i)
+                ring_load16(r, dst + i * (WAVES * 1024), a_chunk[i] * VECE < rem ? a_voff[U == U_A1][i] : kOOB);
+        } else if constexpr (BT) {
+            const i32x4_t r = ring_rsrc(b_base + int64_t(kt) * kStageKBytes, rem > 0 ? bt_bytes : 0u);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                ring_load16(r, dst + i * (WAVES * 1024), b_chunk[i] * VECE < rem ? b_voff[U == U_B1][i] : kOOB);
         } else {
+            const int rows = rem <= 0 ? 0 : (rem < BK ? rem : BK);
+            // readfirstlane: the compiler otherwise clamps the (uniform) size on the vector unit
+            const i32x4_t r = ring_rsrc(b_base + int64_t(kt) * BK * ldb_b,
+                                        uint32_t(__builtin_amdgcn_readfirstlane(int(rows * ldb_b))));
 #pragma unroll
-            for (int i = 0; i < A_INSTR; ++i) {
-                const uint32_t off = int64_t(a_chunk[i]) * VECE < rem ? a_voff[i] : kOOB;
-                load_lds16(ra, as + (i * WAVES + wave) * 1024, off);
-                load_lds16(rb, bs + (i * WAVES + wave) * 1024, b_voff[i]);
-            }
+            for (int i = 0; i < 2; ++i) ring_load16(r, dst + i * (WAVES * 1024), b_voff[U == U_B1][i]);
         }
     };
 
-    // fragment offsets (see gemm_lds_kernel)
-    const int frag_row = lane & 31;
-    const int frag_half = lane >> 5;
-    const int wrow0 = wave_m * (BM / 2);
-    const int wcol0 = wave_n * (BN / 4);
-    const int r0 = wrow0 + frag_row;
-    const int f0 = (r0 ^ (r0 >> 3)) & 7;
-    int a_fo[2][4];
+    // ---- fragment offsets within a unit ----
+    const int frag_row = lane & 31, frag_half = lane >> 5;
+    const int ra0 = grp * 64 + frag_row, rb0 = wave_n * 32 + frag_row;
+    int a_fo[4], bt_fo[4];                                 // k-step st of the first 32 rows
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int st = 0; st < 4; ++st) a_fo[p][st] = r0 * kStageKBytes + 16 * ((2 * st + frag_half) ^ f0 ^ (4 * p));
-    const int g16 = lane & 15, lgrp = lane >> 4;
+    for (int st = 0; st < 4; ++st) {
+        a_fo[st] = ra0 * kStageKBytes + 16 * swz(2 * st + frag_half, ra0);
+        bt_fo[st] = rb0 * kStageKBytes + 16 * swz(2 * st + frag_half, rb0);
+    }
+    const int lgrp = lane >> 4, g16 = lane & 15;           // transpose reads, as in gemm_lds_kernel
     constexpr int TR_ROWS = DT == DT_BF16 ? 4 : 8;
     constexpr int KSTEP = 32 / E;
     const int tr_row = DT == DT_BF16 ? (g16 >> 2) : (g16 >> 1);
     const int tr_colb = (DT == DT_BF16 ? (g16 & 3) * 8 : (g16 & 1) * 8) + (lgrp & 1) * 16 * E;
     const int tr_khalf = (lgrp >> 1) * (KSTEP / 2);
-    const int bz = bswz<DT>(tr_row);
-    int b_fo[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int colb = (wcol0 + j * 32) * E + tr_colb;
-        b_fo[j] = (tr_khalf + tr_row) * B_PITCH + (((colb >> 4) ^ bz) << 4) + (colb & 15);
-    }
+    const int b_colb = wave_n * 32 * E + tr_colb;
+    const int b_fo = (tr_khalf + tr_row) * B_PITCH +
+                     (((b_colb >> 4) ^ (BT ? 0 : ring_bswz<DT, B_CPR>(tr_row))) << 4) + (b_colb & 15);
 
-    u32x4_t fa[2][TM], fb[2][TN];                          // one unit: two k-steps
-    auto load_unit = [&](auto buf_c, auto h_c) {
-        constexpr int BUF = decltype(buf_c)::value;
-        constexpr int H = decltype(h_c)::value;
-        const uint8_t *const as = BUF ? a_lds1 : a_lds0;
-        const uint8_t *const bs = BUF ? b_lds1 : b_lds0;
+    u32x4_t fa[2][4], fb[2][4];                            // A: two 32-row tiles; B: halves 0 and 1; four k-steps
+    auto read_a = [&](auto buf_c, auto u_c) {
+        const uint8_t *const p = lds[decltype(buf_c)::value][decltype(u_c)::value];
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            constexpr int dummy = 0; (void)dummy;
-            const int S = 2 * H + ks;
+        for (int st = 0; st < 4; ++st)
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-                fa[ks][i] = *reinterpret_cast<const u32x4_t *>(as + a_fo[i & 1][S] + 4096 * i);
+            // the swizzle of rows 32 further down differs by chunk ^ 4: k-step st ^ 2's chunk
+            for (int i = 0; i < 2; ++i) fa[i][st] = *reinterpret_cast<const u32x4_t *>(p + a_fo[st ^ (2 * i)] + 4096 * i);
+    };
+    auto read_b = [&](auto buf_c, auto u_c) {
+        constexpr int U = decltype(u_c)::value;
+        const uint8_t *const p = lds[decltype(buf_c)::value][U];
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const u32x2_t lo = lds_read_tr<DT>(bs + b_fo[j] + (S * KSTEP) * B_PITCH);
-                const u32x2_t hi = lds_read_tr<DT>(bs + b_fo[j] + (S * KSTEP + TR_ROWS) * B_PITCH);
-                fb[ks][j] = u32x4_t{lo[0], lo[1], hi[0], hi[1]};
+        for (int st = 0; st < 4; ++st) {
+            if constexpr (BT) {
+                fb[U == U_B1][st] = *reinterpret_cast<const u32x4_t *>(p + bt_fo[st]);
+            } else {
+                const u32x2_t lo = lds_read_tr<DT>(p + b_fo + (st * KSTEP) * B_PITCH);
+                const u32x2_t hi = lds_read_tr<DT>(p + b_fo + (st * KSTEP + TR_ROWS) * B_PITCH);
+                fb[U == U_B1][st] = u32x4_t{lo[0], lo[1], hi[0], hi[1]};
             }
         }
     };
@@ -466,61 +486,68 @@ void gemm_pingpong_kernel(KernelArgs args) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = acc_vec{};
 
-    auto compute_unit = [&]() {
+    // Ends a phase's reads and loads, then runs its quadrant (row half H, column half J).
+    auto quadrant = [&](auto h_c, auto j_c) {
+        constexpr int H = decltype(h_c)::value, J = decltype(j_c)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        ring_barrier<12>();
+        __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+        for (int st = 0; st < 4; ++st)
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = mfma32<DT>(fa[ks][i], fb[ks][j], acc[i][j]);
+            for (int i = 0; i < 2; ++i) acc[2 * H + i][J] = mfma32<DT>(fa[i][st], fb[J][st], acc[2 * H + i][J]);
         __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
     };
 
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-
-    // Four phases of stage s (LDS buffer BUF = s % 2).
-    auto stage_phases = [&](int s, auto buf_c) {
-        using OTHER = std::integral_constant<int, 1 - decltype(buf_c)::value>;
-        // phase 4s
-        if (grp == 0) {
-            if (s + 1 < nk) load_stage(s + 1, OTHER{});
-            load_unit(buf_c, I0{});
-        } else if (s > 0) {
-            compute_unit();
-        }
-        phase_barrier();
-        // phase 4s+1
-        if (grp == 0) {
-            compute_unit();
-        } else {
-            if (s + 1 < nk) load_stage(s + 1, OTHER{});
-            load_unit(buf_c, I0{});
-        }
-        phase_barrier();
-        // phase 4s+2
-        if (grp == 0) load_unit(buf_c, I1{});
-        else compute_unit();
-        phase_barrier();
-        // phase 4s+3
-        if (grp == 0) compute_unit();
-        else load_unit(buf_c, I1{});
-        stage_barrier();
+    using B0 = std::integral_constant<int, U_B0>;
+    using A0 = std::integral_constant<int, U_A0>;
+    using B1 = std::integral_constant<int, U_B1>;
+    using A1 = std::integral_constant<int, U_A1>;
+    auto stage = [&](int kt, auto buf_c) {
+        using NEXT = std::integral_constant<int, 1 - decltype(buf_c)::value>;
+        read_a(buf_c, A0{});
+        load_unit(kt + 2, buf_c, B0{});
+        quadrant(I0{}, I0{});
+        read_b(buf_c, B1{});
+        load_unit(kt + 2, buf_c, A0{});
+        quadrant(I0{}, I1{});
+        read_a(buf_c, A1{});
+        load_unit(kt + 2, buf_c, B1{});
+        quadrant(I1{}, I0{});
+        read_b(NEXT{}, B0{});
+        load_unit(kt + 2, buf_c, A1{});
+        quadrant(I1{}, I1{});
     };
 
-    if (nk > 0) {
-        load_stage(0, I0{});
-        stage_barrier();
-        for (int s = 0; s < nk; s += 2) {
-            stage_phases(s, I0{});
-            if (s + 1 < nk) stage_phases(s + 1, I1{});
+    if (ns > 0) {
+        static_for<0, 2>([&](auto s) {
+            load_unit(decltype(s)::value, s, B0{});
+            load_unit(decltype(s)::value, s, A0{});
+            load_unit(decltype(s)::value, s, B1{});
+            load_unit(decltype(s)::value, s, A1{});
+        });
+        ring_barrier<12>();                                // B0 and A0 of stage 0 have landed
+        read_b(I0{}, B0{});
+        phase_barrier();                                   // ... and B0 is read, before phase 1 refills it
+        if (grp == 1) asm volatile("s_barrier" ::: "memory");
+        int kt = 0;
+        for (; kt + 1 < ns; kt += 2) {
+            stage(kt, I0{});
+            stage(kt + 1, I1{});
         }
-        if (grp == 1) compute_unit();                       // group 1's last unit
+        if (kt < ns) stage(kt, I0{});
+        if (grp == 0) asm volatile("s_barrier" ::: "memory");
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // drain the loads past the end before exit
 
     __shared__ int s_last;
-    store_tile<DT, BM, BN, TM, TN>(args, acc, tm, tn, slice, m0 + wrow0, n0 + wcol0, lane, s_last);
+    store_tile<DT, BM, BN, TM, TN, HALF>(args, acc, tm, tn, slice, m0 + grp * 128, n0 + wave_n * 32, lane, s_last);
 }
 
 }  // namespace gemm

@@ -25,8 +25,12 @@ hipError_t launch_direct_family(int32_t cfg, const KernelArgs &a, int64_t grid, 
         case 11: return launch_direct<DT, 256, 256, 4, 2, 2>(a, grid, s);
         case 12: return launch_direct<DT, 128, 256, 2, 4, 2>(a, grid, s);
         case 13:
-            if (a.b_trans) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((gemm_pingpong_kernel<DT>), dim3(unsigned(grid)), dim3(512), 0, s, a);
+        case 44:
+            if (a.b_trans && cfg == 13) return hipErrorInvalidValue;
+            if (a.b_trans)
+                hipLaunchKernelGGL((gemm_pingpong_kernel<DT, true>), dim3(unsigned(grid)), dim3(512), 0, s, a);
+            else
+                hipLaunchKernelGGL((gemm_pingpong_kernel<DT, false>), dim3(unsigned(grid)), dim3(512), 0, s, a);
             return hipGetLastError();
         default: return hipErrorInvalidValue;
     }
