@@ -60,8 +60,8 @@ constexpr int32_t kSlotKBytes = 64;
 // 13, row-major B only (plan files name configurations by index), and 44, both layouts.
 constexpr TileConfig kConfigs[] = {
     // family       bm   bn  wm wn occ stages eff_i8 eff_bf16 colB name
-    {FAM_GENERIC,   64,  64, 2, 2, 4, 2, 0.134, 0.145, 1, "generic_64x64_w4"},
-    {FAM_GENERIC,  128, 128, 2, 2, 2, 2, 0.305, 0.272, 1, "generic_128x128_w4"},
+    {FAM_GENERIC,   64,  64, 2, 2, 4, 2, 0.124, 0.158, 1, "generic_64x64_w4"},
+    {FAM_GENERIC,  128, 128, 2, 2, 2, 2, 0.162, 0.241, 1, "generic_128x128_w4"},
     {FAM_MACRO,    256, 256, 2, 2, 1, 2, 0.33, 0.41, 0, "macro_256x256_w4"},
     {FAM_MACRO,    128, 256, 2, 2, 1, 2, 0.27, 0.33, 0, "macro_128x256_w4"},
     {FAM_MACRO,    256, 128, 2, 2, 1, 2, 0.31, 0.33, 0, "macro_256x128_w4"},
@@ -101,9 +101,9 @@ constexpr TileConfig kConfigs[] = {
     {FAM_RING,     256, 128, 2, 2, 2, 3, 0.36, 0.34, 1, "ring_256x128_w4_r3"},
     {FAM_RING,     128, 256, 1, 4, 2, 3, 0.36, 0.34, 1, "ring_128x256_w4c_r3"},
     {FAM_RING,     128, 256, 2, 4, 2, 3, 0.36, 0.34, 1, "ring_128x256_w8_r3"},
-    {FAM_GENERIC,   32, 128, 1, 4, 4, 2, 0.084, 0.143, 1, "generic_32x128_w4"},
-    {FAM_GENERIC,   64, 128, 1, 4, 3, 2, 0.158, 0.227, 1, "generic_64x128_w4"},
-    {FAM_GENERIC,  256, 128, 4, 2, 1, 2, 0.450, 0.379, 1, "generic_256x128_w8"},
+    {FAM_GENERIC,   32, 128, 1, 4, 4, 2, 0.101, 0.125, 1, "generic_32x128_w4"},
+    {FAM_GENERIC,   64, 128, 1, 4, 3, 2, 0.135, 0.177, 1, "generic_64x128_w4"},
+    {FAM_GENERIC,  256, 128, 4, 2, 1, 2, 0.189, 0.272, 1, "generic_256x128_w8"},
     {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.50, 0.56, 1, "quad_256x256_w8"},
 };
 constexpr int32_t kNumConfigs = int32_t(sizeof(kConfigs) / sizeof(kConfigs[0]));

@@ -168,10 +168,12 @@ void gemm_element_kernel(KernelArgs args) {
 // the last row) takes its pieces through load_tail: read ending at the row's end and
 // shifted down, zero from K on.  It needs rows of at least 16 bytes (wide_rows_ok).
 //
-// A stage's loads are issued half a stage before the one whose LDS writes they feed,
-// so they have a whole stage to land while registers hold only one stage.
+// A stage's loads are issued AHEAD stages and a half before it is read: one set of
+// staging registers for the small tiles, of which several share a CU, two for the
+// large ones.
 //
-// Measured against element-wise loads: bf16 256 x 32003 x 4096, row-major B, 1397 -> 99 us;
+// Measured against element-wise loads: bf16 256 x 32003 x 4096, row-major B, 1397 -> 86 us
+// (94 with one stage in flight; int8 6314 x 932 x 2271 41 -> 35 us by the second);
 // bf16 2047 x 2051 x 2049, column-major B, 350 -> 47 us; int8 50176 x 64 x 147 28.1 -> 6.7 us
 // (kernel time; 8.5 with the host's launch).  The load path bounds it: each misaligned
 // 128-byte row piece touches two lines, so a 256 x 128 tile's stage takes about 2400 clocks
@@ -196,10 +198,11 @@ __device__ __forceinline__ u32x4_t shift_down(u32x4_t v, int s) {
     return u32x4_t{uint32_t(lo), uint32_t(lo >> 32), uint32_t(hi), uint32_t(hi >> 32)};
 }
 
-template <int DT, int BM, int BN, int WM, int WN, bool BT, int WAVES_PER_EU>
+template <int DT, int BM, int BN, int WM, int WN, bool BT, int WAVES_PER_EU, int AHEAD>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN, 64 * WM * WN),
                           amdgpu_waves_per_eu(WAVES_PER_EU, WAVES_PER_EU)))
 void gemm_tile_kernel(KernelArgs args) {
+    static_assert(AHEAD == 1 || AHEAD == 2, "register stages in flight");
     using acc_vec = typename Types<DT>::acc_vec;
     constexpr int E = Types<DT>::E;
     constexpr int VECE = 16 / E;
@@ -258,16 +261,26 @@ void gemm_tile_kernel(KernelArgs args) {
     const uint8_t *const b_base =
         static_cast<const uint8_t *>(args.B) + (BT ? n0 * args.ldb + k_begin : k_begin * args.ldb) * E;
 
-    u32x4_t ra[A_CH], rb[B_CH];
-    // Stage kt into the registers.  reaches_end: the stage holds the end of K.
-    auto load_stage = [&](int kt) {
+    u32x4_t ra_[AHEAD][A_CH], rb_[AHEAD][B_CH];
+    // Stage kt into register set SET: any stage but the one with the end of K ...
+    auto load_full = [&](int kt, auto set_c) {
+        u32x4_t(&ra)[A_CH] = ra_[decltype(set_c)::value];
+        u32x4_t(&rb)[B_CH] = rb_[decltype(set_c)::value];
+        const uint8_t *const ap = a_base + int64_t(kt) * kStageKBytes;
+        const uint8_t *const bp = b_base + (BT ? int64_t(kt) * kStageKBytes : int64_t(kt) * BK * ldb_b);
+#pragma unroll
+        for (int i = 0; i < A_CH; ++i) ra[i] = load_any16(ap, a_voff[i]);
+#pragma unroll
+        for (int i = 0; i < B_CH; ++i) rb[i] = load_any16(bp, b_voff[i]);
+    };
+    // ... and any stage at all.
+    auto load_stage = [&](int kt, auto set_c) {
+        u32x4_t(&ra)[A_CH] = ra_[decltype(set_c)::value];
+        u32x4_t(&rb)[B_CH] = rb_[decltype(set_c)::value];
         const uint8_t *const ap = a_base + int64_t(kt) * kStageKBytes;
         const uint8_t *const bp = b_base + (BT ? int64_t(kt) * kStageKBytes : int64_t(kt) * BK * ldb_b);
         if (kt + 1 < nk || k_end < args.K) {
-#pragma unroll
-            for (int i = 0; i < A_CH; ++i) ra[i] = load_any16(ap, a_voff[i]);
-#pragma unroll
-            for (int i = 0; i < B_CH; ++i) rb[i] = load_any16(bp, b_voff[i]);
+            load_full(kt, set_c);
         } else {
             const int rem = int(k_end - k_begin - int64_t(kt) * BK);          // 1 .. BK
             // K-contiguous rows: bytes past the row's end (offset from this stage's start)
@@ -291,8 +304,10 @@ void gemm_tile_kernel(KernelArgs args) {
         }
     };
     const int a_wr = a_row * kStageKBytes;
-    auto store_stage = [&](auto buf_c) {
+    auto store_stage = [&](auto buf_c, auto set_c) {
         constexpr int BUF = decltype(buf_c)::value;
+        const u32x4_t(&ra)[A_CH] = ra_[decltype(set_c)::value];
+        const u32x4_t(&rb)[B_CH] = rb_[decltype(set_c)::value];
         uint8_t *const as = smem + BUF * (A_STAGE + B_STAGE);
         uint8_t *const bs = as + A_STAGE;
 #pragma unroll
@@ -374,19 +389,25 @@ void gemm_tile_kernel(KernelArgs args) {
     using I2 = std::integral_constant<int, 2>;
     using I3 = std::integral_constant<int, 3>;
 
-    // One stage (LDS buffer BUF holds stage kt, visible; the registers hold stage kt + 1).
+    // One stage (LDS buffer BUF holds stage kt, visible; the registers hold stage kt + 1, and
+    // kt + 2 if two sets are in flight: stage s in set s % AHEAD).
     // Slot 1 carries the last k-step's fragments over the barrier, as in gemm_lds_kernel.
     // The other buffer is free from the barrier that ended stage kt - 1 on.
-    auto stage = [&](int kt, auto buf_c) {
+    // STEADY: stage kt + 1 + AHEAD is a full one, loaded without a branch, so that the waits
+    // before the LDS writes can leave the younger set in flight.
+    auto stage = [&](int kt, auto buf_c, auto steady_c) {
+        constexpr bool STEADY = decltype(steady_c)::value;
         using OTHER = std::integral_constant<int, 1 - decltype(buf_c)::value>;
+        using SET = std::integral_constant<int, OTHER::value % AHEAD>;
         load_frags(buf_c, I0{}, I0{});
         mfma_slot(I1{});
         __builtin_amdgcn_sched_barrier(0);
         load_frags(buf_c, I1{}, I1{});
         mfma_slot(I0{});
         __builtin_amdgcn_sched_barrier(0);
-        if (kt + 1 < nk) store_stage(OTHER{});
-        if (kt + 2 < nk) load_stage(kt + 2);
+        if (STEADY || kt + 1 < nk) store_stage(OTHER{}, SET{});
+        if constexpr (STEADY) load_full(kt + 1 + AHEAD, SET{});
+        else if (kt + 1 + AHEAD < nk) load_stage(kt + 1 + AHEAD, SET{});
         __builtin_amdgcn_sched_barrier(0);
         load_frags(buf_c, I2{}, I0{});
         mfma_slot(I1{});
@@ -397,16 +418,22 @@ void gemm_tile_kernel(KernelArgs args) {
     };
 
     if (nk > 0) {
-        load_stage(0);
-        store_stage(I0{});
-        if (nk > 1) load_stage(1);
+        load_stage(0, I0{});
+        if constexpr (AHEAD == 2)
+            if (nk > 1) load_stage(1, I1{});
+        store_stage(I0{}, I0{});
+        if (nk > AHEAD) load_stage(AHEAD, I0{});
         phase_barrier();
         int kt = 0;
-        for (; kt + 1 < nk; kt += 2) {
-            stage(kt, I0{});
-            stage(kt + 1, I1{});
+        for (; kt + 2 + AHEAD < nk - 1; kt += 2) {
+            stage(kt, I0{}, std::true_type{});
+            stage(kt + 1, I1{}, std::true_type{});
         }
-        if (kt < nk) stage(kt, I0{});
+        for (; kt + 1 < nk; kt += 2) {
+            stage(kt, I0{}, std::false_type{});
+            stage(kt + 1, I1{}, std::false_type{});
+        }
+        if (kt < nk) stage(kt, I0{}, std::false_type{});
         mfma_slot(I1{});
     }
 

@@ -8,11 +8,11 @@
 namespace gemm {
 
 // GENERIC: the 16-byte loader where the operands' rows allow it, else element by element.
-template <int DT, int BM, int BN, int WM, int WN, int WPE>
+template <int DT, int BM, int BN, int WM, int WN, int WPE, int AHEAD>
 static hipError_t launch_any(const KernelArgs &a, int64_t grid, hipStream_t stream) {
     const dim3 g{unsigned(grid)}, b(64 * WM * WN);
-    if (a.b_trans) hipLaunchKernelGGL((gemm_tile_kernel<DT, BM, BN, WM, WN, true, WPE>), g, b, 0, stream, a);
-    else hipLaunchKernelGGL((gemm_tile_kernel<DT, BM, BN, WM, WN, false, WPE>), g, b, 0, stream, a);
+    if (a.b_trans) hipLaunchKernelGGL((gemm_tile_kernel<DT, BM, BN, WM, WN, true, WPE, AHEAD>), g, b, 0, stream, a);
+    else hipLaunchKernelGGL((gemm_tile_kernel<DT, BM, BN, WM, WN, false, WPE, AHEAD>), g, b, 0, stream, a);
     return hipGetLastError();
 }
 
@@ -46,17 +46,17 @@ hipError_t launch_tile_family(int32_t cfg, const KernelArgs &a, int64_t grid, hi
         }
     }
     switch (cfg) {
-        case 0: return launch_any<DT, 64, 64, 2, 2, 4>(a, grid, s);
-        case 1: return launch_any<DT, 128, 128, 2, 2, 2>(a, grid, s);
+        case 0: return launch_any<DT, 64, 64, 2, 2, 4, 1>(a, grid, s);
+        case 1: return launch_any<DT, 128, 128, 2, 2, 2, 2>(a, grid, s);
         case 2: return launch_vec<DT, 256, 256, 2, 2, 1>(a, grid, s);
         case 3: return launch_vec<DT, 128, 256, 2, 2, 1>(a, grid, s);
         case 4: return launch_vec<DT, 256, 128, 2, 2, 1>(a, grid, s);
         case 5: return launch_vec<DT, 128, 128, 2, 2, 2>(a, grid, s);
         case 6: return launch_vec<DT, 32, 256, 1, 4, 2>(a, grid, s);
         case 7: return launch_vec<DT, 64, 256, 1, 4, 2>(a, grid, s);
-        case 41: return launch_any<DT, 32, 128, 1, 4, 4>(a, grid, s);
-        case 42: return launch_any<DT, 64, 128, 1, 4, 3>(a, grid, s);
-        case 43: return launch_any<DT, 256, 128, 4, 2, 2>(a, grid, s);
+        case 41: return launch_any<DT, 32, 128, 1, 4, 4, 1>(a, grid, s);
+        case 42: return launch_any<DT, 64, 128, 1, 4, 3, 1>(a, grid, s);
+        case 43: return launch_any<DT, 256, 128, 4, 2, 2, 2>(a, grid, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -129,9 +129,9 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     double overhead_us = double(rounds) * chip.tile_overhead_us / c.occupancy;
     // GENERIC: latency-bound loops, so a workgroup speeds up where the last round leaves it
     // fewer neighbours on its CU, and tiles pay for their outputs (stores of odd rows) more
-    // than for a round.  Fitted on 95 calls of odd sizes (decode, prefill, dense, patches;
-    // every configuration and split timed): the choice runs 1.03x the measured best, the
-    // whole-round model above 1.13x.
+    // than for a round.  Fitted on 113 calls of odd sizes (decode, prefill, dense,
+    // patches; every configuration and split timed): the choice runs 1.03x the measured
+    // best, the whole-round model above 1.15x.
     if (c.family == FAM_GENERIC) {
         const int64_t full = pl.grid / slots, last = pl.grid % slots;
         const double resident = last ? double(std::min<int64_t>(c.occupancy, ceil_div(last, chip.cus))) : 0.0;

@@ -42,9 +42,9 @@ struct Chip {
     double  tile_overhead_us = 2.0;       // per round of workgroups: the first loads' latency and
                                           // the C stores, which the K loop does not hide
     // GENERIC kernels (fitted together with their efficiencies, below):
-    double  generic_solo = 0.53;          // time of a workgroup alone on a CU, as a fraction of its time
+    double  generic_solo = 0.36;          // time of a workgroup alone on a CU, as a fraction of its time
                                           // with the CU full
-    double  generic_us_per_kilo_output = 0.96;  // prologue and C stores, per 1024 outputs of a tile
+    double  generic_us_per_kilo_output = 0.35;  // prologue and C stores, per 1024 outputs of a tile
 };
 
 int32_t elem_bytes(int32_t dtype);
