@@ -215,14 +215,12 @@ __device__ __forceinline__ int32_t requant_nearest_even(int32_t v, int shift, in
     return n < lo ? lo : (n > hi ? hi : n);
 }
 
-// fp32 -> bf16, round to nearest with ties to even.  A NaN keeps its upper half with
-// the quiet bit set (adding the rounding bias to a NaN could carry it into an
-// infinity, a zero or the sign); an infinity and a finite value past the largest
-// bf16 both land on the infinity.
+// fp32 -> bf16, round to nearest with ties to even: the hardware conversion
+// (v_cvt_pk_bf16_f32).  Over all 2^32 inputs it gives the bits of the integer form it
+// replaced: a NaN keeps its sign and upper half with the quiet bit set, subnormals are
+// kept, and a finite value past the largest bf16 lands on the infinity.
 __device__ __forceinline__ uint16_t bf16_nearest_even(float f) {
-    const uint32_t u = __float_as_uint(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return uint16_t((u >> 16) | 0x40u);
-    return uint16_t((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+    return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f));
 }
 
 // Element type of C under epilogue EPI.
@@ -428,7 +426,7 @@ template <int DT, int EPI, int WAVES, int CS, int TM, int TN>
 __device__ __forceinline__ void store_c_direct(const KernelArgs &args,
                                                const typename Types<DT>::acc_vec (&acc)[TM][TN],
                                                int64_t r0, int64_t c0, int lane) {
-    constexpr bool WIDE = WAVES <= 4 && TM * TN <= 4;
+    constexpr bool WIDE = TM * TN <= (EPI != EPI_NONE ? 8 : WAVES <= 4 ? 4 : 0);
     constexpr int64_t LINE = 128 / int64_t(sizeof(typename OutElem<DT, EPI>::type));
     if (args.ldc % LINE == 0 && reinterpret_cast<uintptr_t>(args.C) % 128 == 0) {
         if constexpr (WIDE) store_c_wide<DT, EPI, true, CS>(args, acc, r0, c0, lane);
