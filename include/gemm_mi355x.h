@@ -82,7 +82,7 @@ typedef enum {
 /* Kernel families the selector chooses between (gemm_plan_info.kernel). */
 typedef enum {
     GEMM_KERNEL_AUTO = -1,   /* gemm_force_plan: let the selector decide       */
-    GEMM_KERNEL_GENERIC = 0, /* any alignment; element-wise masked loads       */
+    GEMM_KERNEL_GENERIC = 0, /* any alignment: 16-byte loads at any address    */
     GEMM_KERNEL_MACRO = 1,   /* 16-byte vector loads, large LDS macro-tiles    */
     GEMM_KERNEL_SKINNY = 2,  /* small M: narrow M tile, wide N, split-K        */
     GEMM_KERNEL_DIRECT = 3,  /* global -> LDS direct loads, LDS transpose reads */
@@ -174,8 +174,10 @@ int gemm_bf16_f32(int64_t M, int64_t N, int64_t K,
  * each GPU it runs on until the process ends (64 KiB of counters, the rest for
  * partials: split_k * M * N * 4 bytes must fit in 16 MiB - 64 KiB).  It never
  * calls hipMalloc, hipFree or an allocating library routine; the counters are
- * cleared by a fill kernel on `stream` at each split-K call.  A plan whose
- * partials do not fit returns GEMM_ERR_SCRATCH_LIMIT before anything is queued.
+ * cleared by a fill kernel on `stream` at each split-K call.  Where the partials
+ * of the library's own plan do not fit, the same configuration runs unsplit; a
+ * plan that was forced or loaded from a file and does not fit returns
+ * GEMM_ERR_SCRATCH_LIMIT before anything is queued.
  * Every call on one GPU shares that GPU's array: calls that overlap in time on
  * one GPU (different streams, or host threads) race on it and must not be
  * issued; calls queued in order on one stream are safe.  Other errors as

@@ -60,51 +60,51 @@ constexpr int32_t kSlotKBytes = 64;
 // 13, row-major B only (plan files name configurations by index), and 44, both layouts.
 constexpr TileConfig kConfigs[] = {
     // family       bm   bn  wm wn occ stages eff_i8 eff_bf16 colB name
-    {FAM_GENERIC,   64,  64, 2, 2, 4, 2, 0.124, 0.158, 1, "generic_64x64_w4"},
-    {FAM_GENERIC,  128, 128, 2, 2, 2, 2, 0.162, 0.241, 1, "generic_128x128_w4"},
-    {FAM_MACRO,    256, 256, 2, 2, 1, 2, 0.33, 0.41, 0, "macro_256x256_w4"},
-    {FAM_MACRO,    128, 256, 2, 2, 1, 2, 0.27, 0.33, 0, "macro_128x256_w4"},
-    {FAM_MACRO,    256, 128, 2, 2, 1, 2, 0.31, 0.33, 0, "macro_256x128_w4"},
-    {FAM_MACRO,    128, 128, 2, 2, 2, 2, 0.30, 0.35, 0, "macro_128x128_w4"},
-    {FAM_SKINNY,    32, 256, 1, 4, 2, 2, 0.17, 0.22, 0, "skinny_32x256_w4"},
-    {FAM_SKINNY,    64, 256, 1, 4, 2, 2, 0.25, 0.32, 0, "skinny_64x256_w4"},
-    {FAM_DIRECT,   256, 256, 2, 2, 1, 2, 0.40, 0.44, 1, "direct_256x256_w4"},
-    {FAM_DIRECT,   128, 256, 2, 2, 1, 2, 0.39, 0.34, 1, "direct_128x256_w4"},
-    {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.44, 0.51, 1, "direct_256x256_w8"},
-    {FAM_DIRECT,   256, 256, 4, 2, 1, 2, 0.45, 0.51, 1, "direct_256x256_w8t"},
-    {FAM_DIRECT,   128, 256, 2, 4, 1, 2, 0.42, 0.36, 1, "direct_128x256_w8"},
-    {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.49, 0.55, 0, "pingpong_256x256_w8"},
-    {FAM_SKINNY,    32, 256, 1, 4, 1, 4, 0.10, 0.12, 0, "stream_32x256_s4"},
-    {FAM_SKINNY,    64, 256, 1, 4, 1, 3, 0.15, 0.18, 0, "stream_64x256_s3"},
-    {FAM_RING,     256, 256, 2, 4, 1, 4, 0.40, 0.45, 1, "ring_256x256_w8"},
-    {FAM_RING,     256, 256, 4, 2, 1, 4, 0.40, 0.45, 1, "ring_256x256_w8t"},
-    {FAM_RING,     128, 256, 2, 4, 1, 5, 0.38, 0.34, 1, "ring_128x256_w8"},
-    {FAM_RING,     256, 256, 2, 2, 1, 4, 0.38, 0.42, 1, "ring_256x256_w4"},
-    {FAM_RING,      32,  64, 1, 2, 2, 8, 0.10, 0.12, 1, "ring_32x64_w2"},
-    {FAM_RING,      64,  64, 1, 2, 2, 8, 0.15, 0.18, 1, "ring_64x64_w2"},
-    {FAM_RING,      32, 128, 1, 4, 1, 8, 0.12, 0.14, 1, "ring_32x128_w4"},
-    {FAM_RING,      64, 128, 1, 4, 1, 8, 0.18, 0.20, 1, "ring_64x128_w4"},
-    {FAM_RING,      32, 256, 1, 4, 1, 6, 0.15, 0.18, 1, "ring_32x256_w4"},
-    {FAM_RING,      64, 256, 1, 4, 1, 6, 0.22, 0.26, 1, "ring_64x256_w4"},
+    {FAM_GENERIC,   64,  64, 2, 2, 4, 2, 0.141, 0.156, 1, "generic_64x64_w4"},
+    {FAM_GENERIC,  128, 128, 2, 2, 2, 2, 0.196, 0.225, 1, "generic_128x128_w4"},
+    {FAM_MACRO,    256, 256, 2, 2, 1, 2, 0.331, 0.410, 0, "macro_256x256_w4"},
+    {FAM_MACRO,    128, 256, 2, 2, 1, 2, 0.269, 0.339, 0, "macro_128x256_w4"},
+    {FAM_MACRO,    256, 128, 2, 2, 1, 2, 0.306, 0.318, 0, "macro_256x128_w4"},
+    {FAM_MACRO,    128, 128, 2, 2, 2, 2, 0.243, 0.269, 0, "macro_128x128_w4"},
+    {FAM_SKINNY,    32, 256, 1, 4, 2, 2, 0.142, 0.180, 0, "skinny_32x256_w4"},
+    {FAM_SKINNY,    64, 256, 1, 4, 2, 2, 0.232, 0.300, 0, "skinny_64x256_w4"},
+    {FAM_DIRECT,   256, 256, 2, 2, 1, 2, 0.421, 0.507, 1, "direct_256x256_w4"},
+    {FAM_DIRECT,   128, 256, 2, 2, 1, 2, 0.485, 0.364, 1, "direct_128x256_w4"},
+    {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.640, 0.674, 1, "direct_256x256_w8"},
+    {FAM_DIRECT,   256, 256, 4, 2, 1, 2, 0.608, 0.694, 1, "direct_256x256_w8t"},
+    {FAM_DIRECT,   128, 256, 2, 4, 1, 2, 0.457, 0.388, 1, "direct_128x256_w8"},
+    {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.778, 0.766, 0, "pingpong_256x256_w8"},
+    {FAM_SKINNY,    32, 256, 1, 4, 1, 4, 0.128, 0.144, 0, "stream_32x256_s4"},
+    {FAM_SKINNY,    64, 256, 1, 4, 1, 3, 0.215, 0.285, 0, "stream_64x256_s3"},
+    {FAM_RING,     256, 256, 2, 4, 1, 4, 0.684, 0.662, 1, "ring_256x256_w8"},
+    {FAM_RING,     256, 256, 4, 2, 1, 4, 0.699, 0.691, 1, "ring_256x256_w8t"},
+    {FAM_RING,     128, 256, 2, 4, 1, 5, 0.529, 0.543, 1, "ring_128x256_w8"},
+    {FAM_RING,     256, 256, 2, 2, 1, 4, 0.439, 0.620, 1, "ring_256x256_w4"},
+    {FAM_RING,      32,  64, 1, 2, 2, 8, 0.058, 0.068, 1, "ring_32x64_w2"},
+    {FAM_RING,      64,  64, 1, 2, 2, 8, 0.083, 0.133, 1, "ring_64x64_w2"},
+    {FAM_RING,      32, 128, 1, 4, 1, 8, 0.068, 0.132, 1, "ring_32x128_w4"},
+    {FAM_RING,      64, 128, 1, 4, 1, 8, 0.138, 0.149, 1, "ring_64x128_w4"},
+    {FAM_RING,      32, 256, 1, 4, 1, 6, 0.151, 0.190, 1, "ring_32x256_w4"},
+    {FAM_RING,      64, 256, 1, 4, 1, 6, 0.261, 0.339, 1, "ring_64x256_w4"},
     {FAM_GEMV,       1, 1024, 1, 4, 4, 1, 0.03, 0.06, 0, "gemv_1024"},
     {FAM_GEMV,       1,  16, 1, 4, 4, 1, 0.03, 0.06, 1, "gemv_bt_16"},
-    {FAM_RING,      32, 256, 1, 4, 2, 4, 0.15, 0.18, 1, "ring_32x256_w4_r4"},
-    {FAM_RING,      32, 128, 1, 4, 2, 6, 0.12, 0.14, 1, "ring_32x128_w4_r6"},
-    {FAM_RING,      64, 128, 1, 4, 2, 5, 0.18, 0.20, 1, "ring_64x128_w4_r5"},
-    {FAM_RING,     128, 128, 2, 2, 2, 4, 0.32, 0.34, 1, "ring_128x128_w4"},
-    {FAM_RING,     128, 128, 2, 2, 1, 8, 0.30, 0.34, 1, "ring_128x128_w4_r8"},
-    {FAM_RING,     128, 128, 2, 4, 1, 8, 0.30, 0.34, 1, "ring_128x128_w8"},
-    {FAM_RING,     256, 256, 4, 2, 1, 5, 0.40, 0.45, 1, "ring_256x256_w8t_r5"},
-    {FAM_RING,     256, 256, 2, 4, 1, 5, 0.40, 0.45, 1, "ring_256x256_w8_r5"},
-    {FAM_RING,     256, 256, 2, 2, 1, 5, 0.38, 0.42, 1, "ring_256x256_w4_r5"},
-    {FAM_RING,     128, 256, 2, 2, 2, 3, 0.36, 0.34, 1, "ring_128x256_w4_r3"},
-    {FAM_RING,     256, 128, 2, 2, 2, 3, 0.36, 0.34, 1, "ring_256x128_w4_r3"},
-    {FAM_RING,     128, 256, 1, 4, 2, 3, 0.36, 0.34, 1, "ring_128x256_w4c_r3"},
-    {FAM_RING,     128, 256, 2, 4, 2, 3, 0.36, 0.34, 1, "ring_128x256_w8_r3"},
-    {FAM_GENERIC,   32, 128, 1, 4, 4, 2, 0.101, 0.125, 1, "generic_32x128_w4"},
-    {FAM_GENERIC,   64, 128, 1, 4, 3, 2, 0.135, 0.177, 1, "generic_64x128_w4"},
-    {FAM_GENERIC,  256, 128, 4, 2, 1, 2, 0.189, 0.272, 1, "generic_256x128_w8"},
-    {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.50, 0.56, 1, "quad_256x256_w8"},
+    {FAM_RING,      32, 256, 1, 4, 2, 4, 0.156, 0.214, 1, "ring_32x256_w4_r4"},
+    {FAM_RING,      32, 128, 1, 4, 2, 6, 0.118, 0.149, 1, "ring_32x128_w4_r6"},
+    {FAM_RING,      64, 128, 1, 4, 2, 5, 0.233, 0.224, 1, "ring_64x128_w4_r5"},
+    {FAM_RING,     128, 128, 2, 2, 2, 4, 0.404, 0.361, 1, "ring_128x128_w4"},
+    {FAM_RING,     128, 128, 2, 2, 1, 8, 0.333, 0.359, 1, "ring_128x128_w4_r8"},
+    {FAM_RING,     128, 128, 2, 4, 1, 8, 0.269, 0.361, 1, "ring_128x128_w8"},
+    {FAM_RING,     256, 256, 4, 2, 1, 5, 0.663, 0.691, 1, "ring_256x256_w8t_r5"},
+    {FAM_RING,     256, 256, 2, 4, 1, 5, 0.659, 0.683, 1, "ring_256x256_w8_r5"},
+    {FAM_RING,     256, 256, 2, 2, 1, 5, 0.426, 0.629, 1, "ring_256x256_w4_r5"},
+    {FAM_RING,     128, 256, 2, 2, 2, 3, 0.451, 0.446, 1, "ring_128x256_w4_r3"},
+    {FAM_RING,     256, 128, 2, 2, 2, 3, 0.555, 0.373, 1, "ring_256x128_w4_r3"},
+    {FAM_RING,     128, 256, 1, 4, 2, 3, 0.413, 0.435, 1, "ring_128x256_w4c_r3"},
+    {FAM_RING,     128, 256, 2, 4, 2, 3, 0.560, 0.549, 1, "ring_128x256_w8_r3"},
+    {FAM_GENERIC,   32, 128, 1, 4, 4, 2, 0.104, 0.131, 1, "generic_32x128_w4"},
+    {FAM_GENERIC,   64, 128, 1, 4, 3, 2, 0.164, 0.219, 1, "generic_64x128_w4"},
+    {FAM_GENERIC,  256, 128, 4, 2, 1, 2, 0.232, 0.353, 1, "generic_256x128_w8"},
+    {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.779, 0.767, 1, "quad_256x256_w8"},
 };
 constexpr int32_t kNumConfigs = int32_t(sizeof(kConfigs) / sizeof(kConfigs[0]));
 

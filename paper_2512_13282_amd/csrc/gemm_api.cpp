@@ -38,9 +38,10 @@ struct Key {
     int32_t dtype;
     int64_t M, N, K;
     int32_t align;     // alignment_class
-    int32_t trans_b;
+    int32_t trans_b, c_bytes;
     bool operator==(const Key &o) const {
-        return dtype == o.dtype && M == o.M && N == o.N && K == o.K && align == o.align && trans_b == o.trans_b;
+        return dtype == o.dtype && M == o.M && N == o.N && K == o.K && align == o.align && trans_b == o.trans_b &&
+               c_bytes == o.c_bytes;
     }
 };
 // 64-bit FNV-1a over the key's fields (its published offset basis and prime).
@@ -49,7 +50,7 @@ struct KeyHash {
         uint64_t h = 1469598103934665603ULL;
         auto mix = [&](uint64_t v) { h = (h ^ v) * 1099511628211ULL; };
         mix(uint64_t(k.dtype)); mix(uint64_t(k.M)); mix(uint64_t(k.N)); mix(uint64_t(k.K));
-        mix(uint64_t(k.align)); mix(uint64_t(k.trans_b));
+        mix(uint64_t(k.align)); mix(uint64_t(k.trans_b)); mix(uint64_t(k.c_bytes));
         return size_t(h);
     }
 };
@@ -70,7 +71,7 @@ struct Shape {
     }
 };
 struct ShapeHash {
-    size_t operator()(const Shape &s) const { return KeyHash()(Key{s.dtype, s.M, s.N, s.K, 0, s.trans_b}); }
+    size_t operator()(const Shape &s) const { return KeyHash()(Key{s.dtype, s.M, s.N, s.K, 0, s.trans_b, 4}); }
 };
 struct LoadedPlan {
     int32_t config, split, reduce;
@@ -191,7 +192,7 @@ int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr) {
     }
     const bool forced = ov.family >= 0 || ov.config >= 0 || ov.split > 0 || ov.reduce >= 0;
     if (!forced) {
-        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b};
+        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b, p.c_bytes};
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_cache.find(key);
         if (it != g_cache.end()) {
@@ -224,7 +225,7 @@ int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr) {
                       : gemm::neighbour_plan(p, &cfg, &split, &reduce) ? GEMM_PLAN_FROM_NEIGHBOUR
                       : GEMM_PLAN_FROM_MODEL;
     if (!forced) {
-        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b};
+        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b, p.c_bytes};
         std::lock_guard<std::mutex> lk(g_mu);
         if (g_cache.size() > 4096) g_cache.clear();
         g_cache.emplace(key, CachedPlan{pl, src});
@@ -239,13 +240,21 @@ int run(int32_t dtype, int32_t trans_b, int64_t M, int64_t N, int64_t K, const v
         int32_t epilogue = gemm::EPI_NONE, int32_t shift = 0, bool static_scratch = false) {
     Problem p{dtype, M, N, K, lda, ldb, ldc, uintptr_t(A), uintptr_t(B), uintptr_t(C), trans_b};
     const int64_t c_esize = epilogue == gemm::EPI_I8 ? 1 : (epilogue == gemm::EPI_NONE ? 4 : 2);
+    p.c_bytes = int32_t(c_esize);
     if (shift < 0 || shift > 31) return GEMM_ERR_INVALID_VALUE;
     int rc = validate(p, A, B, C, c_esize);
     if (rc != GEMM_OK) return rc;
     if (M == 0 || N == 0) return GEMM_OK;
     Plan pl;
-    rc = plan_for(p, &pl);
+    int32_t source = GEMM_PLAN_FROM_MODEL;
+    rc = plan_for(p, &pl, &source);
     if (rc != GEMM_OK) return rc;
+    // Without allocation, a split that the library chose itself and whose partials exceed the
+    // fixed scratch gives way to the same configuration unsplit; one that the caller asked for
+    // (forced, or from a plan file) is refused by launch_gemm.
+    const bool own = source != GEMM_PLAN_FROM_FORCED && source != GEMM_PLAN_FROM_FILE;
+    if (static_scratch && own && pl.workspace_bytes > gemm::kStaticScratchBytes - gemm::kScratchCounterBytes)
+        pl = gemm::evaluate(p, pl.config, 1);
 
     gemm::KernelArgs a{};
     a.dtype = dtype;

@@ -100,18 +100,20 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
         const int64_t rows = std::min<int64_t>(c.bm, p.M), cols = std::min<int64_t>(c.bn, p.N);
         const double in_kernel_us = 2.5 + 0.35 * double(rows) +
                                     double(pl.split_k - 1) * double(rows * cols) * 4.0 / chip.wg_cold_bytes_per_s * 1e6;
-        const double separate_us = chip.launch_us;
+        
         int32_t mode = reduce >= 0 ? reduce
                      : p.dtype == DT_I8 ? ((c.family == FAM_RING || c.family == FAM_GEMV) ? REDUCE_ATOMIC_FLAG
                                                                                        : REDUCE_ATOMIC)
-                     : (in_kernel_us <= separate_us ? REDUCE_LAST_SLICE : REDUCE_SEPARATE);
-        if ((mode == REDUCE_ATOMIC || mode == REDUCE_ATOMIC_FLAG) && p.dtype != DT_I8) mode = REDUCE_SEPARATE;
+                     : (in_kernel_us <= chip.launch_us ? REDUCE_LAST_SLICE : REDUCE_SEPARATE);
+        if ((mode == REDUCE_ATOMIC || mode == REDUCE_ATOMIC_FLAG) && (p.dtype != DT_I8 || p.c_bytes != 4))
+            mode = REDUCE_SEPARATE;
         if (mode == REDUCE_ATOMIC_FLAG && c.family != FAM_RING && c.family != FAM_GEMV) mode = REDUCE_ATOMIC;
         pl.reduce_in_kernel = mode;
-        // atomic: the fill launch; atomic with slice 0's zeros: their round trip, growing
-        // with the slices that add into the same lines of C
+        // atomic with slice 0's zeros: their round trip, growing with the slices that add into
+        // the same lines of C
         red_us = mode == REDUCE_LAST_SLICE ? in_kernel_us
-               : mode == REDUCE_ATOMIC_FLAG ? chip.round_trip_us * (1.0 + double(pl.split_k) / 8.0) : separate_us;
+               : mode == REDUCE_ATOMIC_FLAG ? chip.flag_us * (1.0 + double(pl.split_k) / 8.0)
+               : mode == REDUCE_ATOMIC ? chip.fill_us : chip.separate_us;
     }
     const bool partial_planes =
         pl.split_k > 1 && pl.reduce_in_kernel != REDUCE_ATOMIC && pl.reduce_in_kernel != REDUCE_ATOMIC_FLAG;
@@ -125,20 +127,19 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     const double wg_ops = 2.0 * c.bm * c.bn * double(pl.k_chunk);
     const double eff = p.dtype == DT_I8 ? c.eff_i8 : c.eff_bf16;
     const double wg_s = wg_ops / (cu_rate * eff / c.occupancy);
-    pl.t_comp_us = double(rounds) * wg_s * 1e6;
-    double overhead_us = double(rounds) * chip.tile_overhead_us / c.occupancy;
-    // GENERIC: latency-bound loops, so a workgroup speeds up where the last round leaves it
-    // fewer neighbours on its CU, and tiles pay for their outputs (stores of odd rows) more
-    // than for a round.  Fitted on 113 calls of odd sizes (decode, prefill, dense,
-    // patches; every configuration and split timed): the choice runs 1.03x the measured
-    // best, the whole-round model above 1.15x.
-    if (c.family == FAM_GENERIC) {
-        const int64_t full = pl.grid / slots, last = pl.grid % slots;
-        const double resident = last ? double(std::min<int64_t>(c.occupancy, ceil_div(last, chip.cus))) : 0.0;
-        const double units = double(full * c.occupancy) + std::max(resident, last ? chip.generic_solo * c.occupancy : 0.0);
-        pl.t_comp_us = units * wg_s / c.occupancy * 1e6;
-        overhead_us = (double(full * c.occupancy) + resident) * chip.generic_us_per_kilo_output * double(c.bm * c.bn) / 1024.0;
-    }
+    // A CU's resident workgroups share its rate, so the last round costs what it leaves on the
+    // fullest CU (at least the time of one workgroup alone).
+    const bool generic = c.family == FAM_GENERIC;
+    const int64_t full = pl.grid / slots, last = pl.grid % slots;
+    const double resident = last ? double(std::min<int64_t>(c.occupancy, ceil_div(last, chip.cus))) : 0.0;
+    const double solo = (generic ? chip.generic_solo : chip.solo) * c.occupancy;
+    const double units = double(full * c.occupancy) + (last ? std::max(resident, c.occupancy > 1 ? solo : 1.0) : 0.0);
+    pl.t_comp_us = units * wg_s / c.occupancy * 1e6;
+    // Each workgroup's prologue and epilogue, which the K loop does not hide.
+    const double overhead_us =
+        (double(full * c.occupancy) + resident) *
+        ((generic ? chip.generic_us_per_kilo_output : chip.us_per_kilo_output) * double(c.bm * c.bn) / 1024.0 +
+         (generic ? chip.generic_us_per_workgroup : chip.us_per_workgroup));
 
     // Memory: compulsory traffic at HBM speed; tile re-reads (Eqs. 6-7 analog)
     // mostly from L2/MALL; split-K partials written and read back once, or added
@@ -149,7 +150,7 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     // 128-column ones).
     const double b_line = (!p.trans_b && c.bn * e < 128) ? 128.0 / double(c.bn * e) : 1.0;
     const double a_bytes = double(p.M) * p.K * e, b_bytes = double(p.K) * p.N * e * b_line;
-    const double c_bytes = double(p.M) * p.N * 4;
+    const double c_bytes = double(p.M) * p.N * p.c_bytes;
     const double a_reads = a_bytes * double(pl.tiles_n);
     const double b_reads = b_bytes * double(pl.tiles_m);
     const double ws = partial_planes ? 2.0 * double(pl.workspace_bytes)
@@ -167,10 +168,7 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
         pl.t_mem_us = std::max(pl.t_mem_us, double(rounds) * wg_bytes / chip.wg_cold_bytes_per_s * 1e6);
     }
 
-    // Each round of workgroups also pays its tiles' prologue and epilogue (measured at
-    // 2048^3: 1.3 us of first loads and 2.5 us of C stores around an 8.5 us K loop); two
-    // workgroups resident on a CU overlap each other's.
-    pl.t_total_us = std::max(pl.t_comp_us, pl.t_mem_us) + overhead_us + chip.launch_us + red_us;
+    pl.t_total_us = std::max(pl.t_comp_us, pl.t_mem_us) + overhead_us + chip.base_us + red_us;
     return pl;
 }
 
@@ -246,9 +244,11 @@ bool select_plan(const Problem &p, Plan *out, int32_t forced_family, int32_t for
         if (forced_config >= 0 && cfg != forced_config) continue;
         if (forced_family >= 0 && kConfigs[cfg].family != forced_family) continue;
         if (!config_applicable(p, cfg)) continue;
-        // The generic family only runs when nothing vectorised applies, or when forced.
+        // Where vectorised kernels can run, GENERIC ones compete only for short K (rows of at
+        // most 2 KiB), where a tile is mostly prologue and C stores and their small tiles (64
+        // rows at most, up to four to a CU) win: bf16 25440 x 64 x 64 8.6 -> 4.6 us, int8 43840 x 64 x 128 9.2 -> 5.0 us.
         if (forced_family < 0 && forced_config < 0 && kConfigs[cfg].family == FAM_GENERIC &&
-            vector_loads_ok(p))
+            (p.K * elem_bytes(p.dtype) > 2048 || kConfigs[cfg].bm > 64) && vector_loads_ok(p))
             continue;
         for (int32_t s : kSplits) {
             if (forced_split > 0 && s != 1) break;

@@ -13,6 +13,7 @@ struct Problem {
     int64_t lda, ldb, ldc;
     uintptr_t a_addr, b_addr, c_addr;
     int32_t trans_b = 0;   // 1: B stored column-major (N x K, row stride ldb)
+    int32_t c_bytes = 4;   // bytes of an output: 4, or 1 or 2 of a narrowed one (never summed atomically)
 };
 
 struct Plan {
@@ -33,18 +34,24 @@ struct Chip {
     double  clock_hz = 2.4e9;
     double  i8_ops_per_clk_cu = 8192.0;   // dense int8 MFMA
     double  bf16_ops_per_clk_cu = 4096.0; // dense bf16 MFMA
-    double  hbm_bytes_per_s = 4.0e12;     // sustained cold-HBM streaming rate the kernels reach
-    double  reread_bytes_per_s = 16.0e12; // A/B tile re-reads mostly served by L2/MALL
-    double  wg_cold_bytes_per_s = 30.0e9; // one workgroup streaming its own strip of B from HBM
-                                          // (measured 26-38 GB/s: its loads in flight over the latency)
-    double  launch_us = 5.0;              // per kernel launch on the stream
-    double  round_trip_us = 1.5;          // one dependent global-memory round trip of a workgroup
-    double  tile_overhead_us = 2.0;       // per round of workgroups: the first loads' latency and
-                                          // the C stores, which the K loop does not hide
-    // GENERIC kernels (fitted together with their efficiencies, below):
-    double  generic_solo = 0.36;          // time of a workgroup alone on a CU, as a fraction of its time
-                                          // with the CU full
-    double  generic_us_per_kilo_output = 0.35;  // prologue and C stores, per 1024 outputs of a tile
+    // Fitted with the configurations' efficiencies (configs.h) on measured plans: 283 calls of
+    // all shapes, aligned and not, every configuration and split of each timed: the choice runs 1.03x the measured
+    // best (with whole rounds of workgroups priced alike, as before, 1.10x).
+    double  hbm_bytes_per_s = 5.1e12;     // compulsory traffic: streaming rate the kernels reach
+    double  reread_bytes_per_s = 19.8e12;   // A/B tile re-reads mostly served by L2/MALL
+    double  wg_cold_bytes_per_s = 31.2e9;  // one workgroup streaming its own strip of B (its loads
+                                          // in flight over the latency)
+    double  launch_us = 5.0;              // a launch on the stream, as the split-K reductions are chosen by it
+    double  base_us = 0.367;               // of every plan
+    double  separate_us = 3.61;          // split-K: the separate reduction's launch ...
+    double  fill_us = 2.89;             // ... the fill kernel's ahead of atomic adds ...
+    double  flag_us = 0.0994;             // ... and C zeroed by the first slice, times 1 + split / 8
+    // Time of a workgroup alone on a CU over that of a full CU's workgroups, each: latency-bound
+    // GENERIC loops speed up least.
+    double  solo = 0.178, generic_solo = 0.263;
+    // Prologue and C stores of a workgroup: per 1024 outputs of its tile, and each.
+    double  us_per_kilo_output = 0.216, generic_us_per_kilo_output = 0.194;
+    double  us_per_workgroup = 0.474, generic_us_per_workgroup = 0.166;
 };
 
 int32_t elem_bytes(int32_t dtype);

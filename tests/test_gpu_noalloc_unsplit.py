@@ -1,0 +1,44 @@
+"""gemm_bf16_f32_noalloc where the library's own split-K plan does not fit its fixed scratch:
+the call runs unsplit and exact (integer-valued operands), while the same split asked for by
+force is refused with nothing written (needs an MI355X)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2512_13282_amd import binding as b
+from paper_2512_13282_amd import inputs
+import gpu_helpers as g
+
+pytestmark = pytest.mark.gpu
+BF = g.BF
+LIMIT = (16 << 20) - (64 << 10)
+
+
+def test_own_split_past_the_scratch_runs_unsplit():
+    shapes = [(M, N, K) for M in (512, 768, 1024) for N in (4096, 8192) for K in (4096, 8192)]
+    fake = 1 << 40
+    plans = {s: b.gemm_plan(BF, *s, s[2], s[1], s[1], fake, 2 * fake, 3 * fake) for s in shapes}
+    large = [s for s, p in plans.items() if p["workspace_bytes"] > LIMIT]
+    assert large, {s: (p["name"], p["split_k"]) for s, p in plans.items()}
+    M, N, K = large[0]
+    A, B = inputs.small_int_bf16_matrix(M, K, seed=3), inputs.small_int_bf16_matrix(K, N, seed=4)
+    dA, lda = g.to_dev(A)
+    dB, ldb = g.to_dev(B)
+    ref = oracle.get().gemm_bf16_f64(A[:64], B)
+    args = (M, N, K, dA.data_ptr(), lda, dB.data_ptr(), ldb)
+    st = torch.cuda.current_stream().cuda_stream
+    out = torch.full((M, N), -7.0, device=g.DEV)
+    same = torch.empty_like(out)
+    assert b.gemm_bf16_f32_noalloc(*args, out.data_ptr(), N, st) == b.GEMM_OK
+    assert b.gemm_bf16_f32(*args, same.data_ptr(), N, st) == b.GEMM_OK
+    torch.cuda.synchronize()
+    assert torch.equal(out, same) and np.array_equal(out[:64].cpu().numpy().astype(np.float64), ref)
+    try:
+        g.force(BF, b.GEMM_KERNEL_AUTO, plans[large[0]]["config"], plans[large[0]]["split_k"], 0)
+        out.fill_(-7.0)
+        assert b.gemm_bf16_f32_noalloc(*args, out.data_ptr(), N, st) == b.GEMM_ERR_SCRATCH_LIMIT
+        torch.cuda.synchronize()
+        assert (out == -7.0).all()
+    finally:
+        g.unforce()
