@@ -29,10 +29,8 @@ struct TileConfig {
     int32_t wm, wn;      // waves along M and N (wave tile = bm/wm x bn/wn)
     int32_t occupancy;   // workgroups resident per CU (LDS and register bound)
     int32_t stages;      // LDS stage buffers
-    double  eff_i8;      // sustained fraction of the 2.4 GHz dense MFMA peak, int8
-    double  eff_bf16;    // same, bf16 (measured on the 8192^3 GEMM, MI355X; ring_128x128_w4's
-                         // int8 figure raised above its 8-slot twin's, which it beats on
-                         // mid-size int8 shapes)
+    double  eff_i8;      // fraction of the 2.4 GHz dense MFMA peak that a CU full of these workgroups
+    double  eff_bf16;    // sustains, int8 and bf16; fitted on timed calls with the model's constants
     int32_t col_major_b; // also compiled for B stored column-major (N x K)
     const char *name;
 };
@@ -105,6 +103,7 @@ constexpr TileConfig kConfigs[] = {
     {FAM_GENERIC,   64, 128, 1, 4, 3, 2, 0.164, 0.219, 1, "generic_64x128_w4"},
     {FAM_GENERIC,  256, 128, 4, 2, 1, 2, 0.232, 0.353, 1, "generic_256x128_w8"},
     {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.779, 0.767, 1, "quad_256x256_w8"},
+    {FAM_DIRECT,    64,  64, 2, 2, 3, 3, 0.130, 0.150, 1, "direct_64x64_w4_s3"},
 };
 constexpr int32_t kNumConfigs = int32_t(sizeof(kConfigs) / sizeof(kConfigs[0]));
 

@@ -310,6 +310,187 @@ void gemm_lds_kernel(KernelArgs args) {
 }
 
 // ---------------------------------------------------------------------------
+// The same kernel for few rows (memory-bound shapes): narrow tiles, NS stages of 128
+// K-bytes in flight, two or more workgroups to a CU.  The narrow ring kernels read a
+// column-major B in 64-byte pieces, half lines that cost HBM and the L2 a whole request
+// each; this one reads whole 128-byte lines and keeps (NS - 1) stages of each workgroup
+// on the way.  Each iteration waits only for its own stage (vmcnt counts the younger
+// stages' loads), then one barrier publishes it and retires the buffer that the next
+// loads overwrite; stages past the end of K load zeros through an empty resource, so
+// every iteration counts the same loads.  LDS layouts and fragment reads are
+// gemm_lds_kernel's (row-major B by the ring's row-width swizzles).
+//
+// Compiled as 64 x 64 with three stages, three workgroups to a CU.  Measured with B from
+// HBM, against the best of the ring kernels: bf16 48 x 11008 x 4096 column-major 25.5
+// against 29.5 us, 64 x 14336 x 4096 column-major bf16 31.8 against 33.3 and int8 17.8
+// against 18.8, bf16 32 x 4096 x 4096 row-major 11.5 against 12.2; 32 x 128 and 64 x 128
+// tiles were behind it.
+// ---------------------------------------------------------------------------
+template <int DT, int BM, int BN, int WM, int WN, int WAVES_PER_EU, bool BT, int NS>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN, 64 * WM * WN),
+                          amdgpu_waves_per_eu(WAVES_PER_EU, WAVES_PER_EU)))
+void gemm_lds_kernel(KernelArgs args) {
+    using acc_vec = typename Types<DT>::acc_vec;
+    constexpr int E = Types<DT>::E;
+    constexpr int VECE = 16 / E;
+    constexpr int BK = kStageKBytes / E;
+    constexpr int WAVES = WM * WN;
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+    constexpr int A_STAGE = BM * kStageKBytes, B_STAGE = BN * kStageKBytes;
+    constexpr int B_PITCH = BT ? kStageKBytes : BN * E;
+    constexpr int B_CPR = B_PITCH / 16;
+    constexpr int A_INSTR = A_STAGE / 1024 / WAVES, B_INSTR = B_STAGE / 1024 / WAVES;
+    constexpr int LPS = A_INSTR + B_INSTR;                 // loads per wave per stage
+    static_assert(A_INSTR >= 1 && A_INSTR * 1024 * WAVES == A_STAGE, "A stage split");
+    static_assert(B_INSTR >= 1 && B_INSTR * 1024 * WAVES == B_STAGE, "B stage split");
+    static_assert(NS >= 3 && (NS - 1) * LPS < 64, "loads in flight must fit vmcnt");
+
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[NS][A_STAGE + B_STAGE];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_m = wave / WN, wave_n = wave % WN;
+
+    int tm, tn, slice;
+    map_tile(args, tm, tn, slice);
+    const int64_t M = args.M, N = args.N;
+    const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
+    const int64_t k_begin = int64_t(slice) * args.k_chunk;
+    int64_t k_end = k_begin + args.k_chunk;
+    if (k_end > args.K) k_end = args.K;
+    const int k_len = k_end > k_begin ? int(k_end - k_begin) : 0;
+    const int nk = (k_len + BK - 1) / BK;
+    const int64_t lda_b = args.lda * E, ldb_b = args.ldb * E;
+
+    const int64_t a_rows_valid = (M - m0) < BM ? (M - m0) : BM;
+    const uint32_t a_bytes = uint32_t(a_rows_valid * lda_b);
+    uint32_t a_voff[A_INSTR];
+    int a_chunk[A_INSTR];
+#pragma unroll
+    for (int i = 0; i < A_INSTR; ++i) {
+        const int row = (i * WAVES + wave) * 8 + (lane >> 3);
+        a_chunk[i] = swz(lane & 7, row);
+        a_voff[i] = uint32_t(row * lda_b + a_chunk[i] * 16);
+    }
+    const int64_t b_rows_valid = (N - n0) < BN ? (N - n0) : BN;
+    const uint32_t bt_bytes = uint32_t(b_rows_valid * ldb_b);
+    uint32_t b_voff[B_INSTR];
+    int b_chunk[B_INSTR];
+#pragma unroll
+    for (int i = 0; i < B_INSTR; ++i) {
+        if constexpr (BT) {
+            const int row = (i * WAVES + wave) * 8 + (lane >> 3);
+            b_chunk[i] = swz(lane & 7, row);
+            b_voff[i] = uint32_t(row * ldb_b + b_chunk[i] * 16);
+        } else {
+            const int row = (i * WAVES + wave) * (1024 / B_PITCH) + lane / B_CPR;
+            const int c = (lane % B_CPR) ^ ring_bswz<DT, B_CPR>(row);
+            b_chunk[i] = 0;
+            b_voff[i] = (n0 + int64_t(c) * VECE < N) ? uint32_t(row * ldb_b + c * 16) : kOOB;
+        }
+    }
+    const uint8_t *const a_base = static_cast<const uint8_t *>(args.A) + (m0 * args.lda + k_begin) * E;
+    const uint8_t *const b_base = static_cast<const uint8_t *>(args.B) +
+                                  (BT ? n0 * args.ldb + k_begin : k_begin * args.ldb + n0) * E;
+
+    auto load_stage = [&](int kt, auto buf_c) {
+        constexpr int BUF = decltype(buf_c)::value;
+        const int rem = k_len - kt * BK;
+        const uint32_t dst = lds_addr(lds[BUF]) + uint32_t(wave) * 1024u;
+        const i32x4_t ra = ring_rsrc(a_base + int64_t(kt) * kStageKBytes, rem > 0 ? a_bytes : 0u);
+#pragma unroll
+        for (int i = 0; i < A_INSTR; ++i)
+            ring_load16(ra, dst + i * (WAVES * 1024), a_chunk[i] * VECE < rem ? a_voff[i] : kOOB);
+        i32x4_t rb;
+        if constexpr (BT) {
+            rb = ring_rsrc(b_base + int64_t(kt) * kStageKBytes, rem > 0 ? bt_bytes : 0u);
+        } else {
+            const int rows = rem <= 0 ? 0 : (rem < BK ? rem : BK);
+            // readfirstlane: the compiler otherwise clamps the (uniform) size on the vector unit
+            rb = ring_rsrc(b_base + int64_t(kt) * BK * ldb_b,
+                           uint32_t(__builtin_amdgcn_readfirstlane(int(rows * ldb_b))));
+        }
+#pragma unroll
+        for (int i = 0; i < B_INSTR; ++i)
+            ring_load16(rb, dst + A_STAGE + i * (WAVES * 1024), (!BT || b_chunk[i] * VECE < rem) ? b_voff[i] : kOOB);
+    };
+
+    const int frag_row = lane & 31, frag_half = lane >> 5;
+    const int wrow0 = wave_m * (BM / WM), wcol0 = wave_n * (BN / WN);
+    const int r0 = wrow0 + frag_row, rb0 = wcol0 + frag_row;
+    int a_fo[4], bt_fo[4];                                 // k-step st of the wave's first 32 rows
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+        a_fo[st] = r0 * kStageKBytes + 16 * swz(2 * st + frag_half, r0);
+        bt_fo[st] = rb0 * kStageKBytes + 16 * swz(2 * st + frag_half, rb0);
+    }
+    const int grp = lane >> 4, g16 = lane & 15;            // transpose reads, as above
+    constexpr int TR_ROWS = DT == DT_BF16 ? 4 : 8;
+    constexpr int KSTEP = 32 / E;
+    const int tr_row = DT == DT_BF16 ? (g16 >> 2) : (g16 >> 1);
+    const int tr_colb = (DT == DT_BF16 ? (g16 & 3) * 8 : (g16 & 1) * 8) + (grp & 1) * 16 * E;
+    const int tr_khalf = (grp >> 1) * (KSTEP / 2);
+    const int bz = BT ? 0 : ring_bswz<DT, B_CPR>(tr_row);
+    int b_fo[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int colb = (wcol0 + j * 32) * E + tr_colb;
+        b_fo[j] = (tr_khalf + tr_row) * B_PITCH + (((colb >> 4) ^ bz) << 4) + (colb & 15);
+    }
+
+    acc_vec acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = acc_vec{};
+
+    auto iteration = [&](int kt, auto buf_c) {
+        constexpr int BUF = decltype(buf_c)::value;
+        ring_barrier<(NS - 2) * LPS>();
+        load_stage(kt + NS - 1, std::integral_constant<int, (BUF + NS - 1) % NS>{});
+        const uint8_t *const as = lds[BUF];
+        const uint8_t *const bs = as + A_STAGE;
+#pragma unroll
+        for (int st = 0; st < 4; ++st) {
+            u32x4_t fa[TM], fb[TN];
+#pragma unroll
+            // rows 32 further down: the chunk of k-step st ^ 2
+            for (int i = 0; i < TM; ++i)
+                fa[i] = *reinterpret_cast<const u32x4_t *>(as + a_fo[st ^ (2 * (i & 1))] + 4096 * i);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if constexpr (BT) {
+                    fb[j] = *reinterpret_cast<const u32x4_t *>(bs + bt_fo[st ^ (2 * (j & 1))] + 4096 * j);
+                } else {
+                    const u32x2_t lo = lds_read_tr<DT>(bs + b_fo[j] + (st * KSTEP) * B_PITCH);
+                    const u32x2_t hi = lds_read_tr<DT>(bs + b_fo[j] + (st * KSTEP + TR_ROWS) * B_PITCH);
+                    fb[j] = u32x4_t{lo[0], lo[1], hi[0], hi[1]};
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = mfma32<DT>(fa[i], fb[j], acc[i][j]);
+        }
+    };
+
+    if (nk > 0) {
+        static_for<0, NS - 1>([&](auto u) { load_stage(decltype(u)::value, u); });
+        for (int kt = 0; kt < nk; kt += NS) {
+            static_for<0, NS>([&](auto u) {
+                if (kt + decltype(u)::value < nk) iteration(kt + decltype(u)::value, u);
+            });
+        }
+    }
+    // Drain the loads past the end, by every wave, before the last-slice flag borrows a word
+    // of the buffers that they write (store_tile synchronises only among later accesses).
+    stage_barrier();
+    store_tile<DT, BM, BN, TM, TN>(args, acc, tm, tn, slice, m0 + wrow0, n0 + wcol0, lane,
+                                   *reinterpret_cast<int *>(lds[0]));
+}
+
+// ---------------------------------------------------------------------------
 // Ping-pong kernel: 256 x 256 macro-tile, 8 waves, two wave groups that alternate
 // between reading fragments and running MFMAs.
 //

@@ -32,6 +32,12 @@ hipError_t launch_direct_family(int32_t cfg, const KernelArgs &a, int64_t grid, 
             else
                 hipLaunchKernelGGL((gemm_pingpong_kernel<DT, false>), dim3(unsigned(grid)), dim3(512), 0, s, a);
             return hipGetLastError();
+        case 45:
+            if (a.b_trans)
+                hipLaunchKernelGGL((gemm_lds_kernel<DT, 64, 64, 2, 2, 3, true, 3>), dim3(unsigned(grid)), dim3(256), 0, s, a);
+            else
+                hipLaunchKernelGGL((gemm_lds_kernel<DT, 64, 64, 2, 2, 3, false, 3>), dim3(unsigned(grid)), dim3(256), 0, s, a);
+            return hipGetLastError();
         default: return hipErrorInvalidValue;
     }
 }

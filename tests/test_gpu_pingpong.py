@@ -1,5 +1,5 @@
-"""The ping-pong kernel (configuration 44, and 13 for row-major B) where its schedule and
-its quadrant layout can go wrong, through the C ABI (needs an MI355X): one to five K
+"""The ping-pong kernel (configuration 44, and 13 for row-major B) and the narrow kernel with
+three stages (45) where their schedules, and the quadrant layout, can go wrong, through the C ABI (needs an MI355X): one to five K
 stages (odd and even counts, ragged last stage, fewer stages than the pipeline holds),
 rows and columns one 16-byte piece past and short of a 32-, 64-, 128- and 256-boundary
 of the tile, and K split so that slices hold different stage counts.  int8 against the
@@ -24,7 +24,8 @@ def _reset_plan():
     g.unforce()
 
 
-@pytest.mark.parametrize("config,bt", [(13, 0), (44, 0), (44, 1)], ids=["13-row", "44-row", "44-col"])
+@pytest.mark.parametrize("config,bt", [(13, 0), (44, 0), (44, 1), (45, 0), (45, 1)],
+                         ids=["13-row", "44-row", "44-col", "45-row", "45-col"])
 @pytest.mark.parametrize("dtype", [I8, BF], ids=["i8", "bf16"])
 def test_stages_and_edges(dtype, config, bt):
     piece = 16 if dtype == I8 else 8
