@@ -25,11 +25,13 @@
 //     broadcasting A tiles along array rows and B tiles along columns
 //     (Sec. 4.2.1).
 //
-// Families: gemm_lds_kernel (DIRECT: global -> LDS buffer loads into two
-// stages), gemm_ring_kernel (RING: the same loads into a ring of 64-byte
-// slots), gemm_vec_kernel / gemm_tile_kernel (MACRO / GENERIC: loads through
-// registers; gemm_element_kernel for GENERIC's shortest rows), gemm_stream_kernel (narrow-M streaming), gemv_kernel and
-// gemv_bt_kernel (M = 1 on the vector ALUs), plus the split-K reduction.
+// Families: gemm_lds_kernel (DIRECT: global -> LDS buffer loads into two stages, or
+// three for few rows), gemm_pingpong_kernel (the same with two wave groups in turn),
+// gemm_ring_kernel (RING: the same loads into a ring of 64-byte slots),
+// gemm_vec_kernel / gemm_tile_kernel (MACRO / GENERIC: loads through registers;
+// gemm_element_kernel for GENERIC's shortest rows), gemm_stream_kernel (narrow-M
+// streaming), gemv_kernel and gemv_bt_kernel (M = 1 on the vector ALUs), plus the
+// split-K reduction.
 //
 // MFMA fragment layout used (32 x 32 output, 64 lanes): lane l supplies row
 // (l mod 32) of the A tile and column (l mod 32) of the B tile, each with 16
@@ -600,23 +602,6 @@ struct TileKernel {
 // c/2, half c%2); int8: row piece = 8 columns (2 dwords, column c in dword
 // c/4, byte c%4).
 // ---------------------------------------------------------------------------
-template <int N>
-__device__ __forceinline__ unsigned bf16_col_dword(const u32x4_t (&rows)[N], int base, int c, int j) {
-    const unsigned lo = rows[base + 2 * j][c >> 1], hi = rows[base + 2 * j + 1][c >> 1];
-    return (c & 1) ? ((lo >> 16) | (hi & 0xFFFF0000u)) : ((lo & 0xFFFFu) | (hi << 16));
-}
-
-template <int N>
-__device__ __forceinline__ unsigned i8_col_dword(const u32x2_t (&rows)[N], int base, int c, int j) {
-    const int sh = 8 * (c & 3);
-    const unsigned b0 = (rows[base + 4 * j + 0][c >> 2] >> sh) & 0xFFu;
-    const unsigned b1 = (rows[base + 4 * j + 1][c >> 2] >> sh) & 0xFFu;
-    const unsigned b2 = (rows[base + 4 * j + 2][c >> 2] >> sh) & 0xFFu;
-    const unsigned b3 = (rows[base + 4 * j + 3][c >> 2] >> sh) & 0xFFu;
-    return b0 | (b1 << 8) | (b2 << 16) | (b3 << 24);
-}
-
-
 // v_perm_b32 byte select: selector byte values 0-3 pick bytes of the SECOND
 // operand, 4-7 bytes of the FIRST.
 __device__ __forceinline__ unsigned perm(unsigned hi, unsigned lo, unsigned sel) {
