@@ -38,10 +38,9 @@ struct Key {
     int32_t dtype;
     int64_t M, N, K;
     int32_t align;     // alignment_class
-    int32_t trans_b, c_bytes;
+    int32_t trans_b;
     bool operator==(const Key &o) const {
-        return dtype == o.dtype && M == o.M && N == o.N && K == o.K && align == o.align && trans_b == o.trans_b &&
-               c_bytes == o.c_bytes;
+        return dtype == o.dtype && M == o.M && N == o.N && K == o.K && align == o.align && trans_b == o.trans_b;
     }
 };
 // 64-bit FNV-1a over the key's fields (its published offset basis and prime).
@@ -50,7 +49,7 @@ struct KeyHash {
         uint64_t h = 1469598103934665603ULL;
         auto mix = [&](uint64_t v) { h = (h ^ v) * 1099511628211ULL; };
         mix(uint64_t(k.dtype)); mix(uint64_t(k.M)); mix(uint64_t(k.N)); mix(uint64_t(k.K));
-        mix(uint64_t(k.align)); mix(uint64_t(k.trans_b)); mix(uint64_t(k.c_bytes));
+        mix(uint64_t(k.align)); mix(uint64_t(k.trans_b));
         return size_t(h);
     }
 };
@@ -71,7 +70,7 @@ struct Shape {
     }
 };
 struct ShapeHash {
-    size_t operator()(const Shape &s) const { return KeyHash()(Key{s.dtype, s.M, s.N, s.K, 0, s.trans_b, 4}); }
+    size_t operator()(const Shape &s) const { return KeyHash()(Key{s.dtype, s.M, s.N, s.K, 0, s.trans_b}); }
 };
 struct LoadedPlan {
     int32_t config, split, reduce;
@@ -192,7 +191,7 @@ int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr) {
     }
     const bool forced = ov.family >= 0 || ov.config >= 0 || ov.split > 0 || ov.reduce >= 0;
     if (!forced) {
-        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b, p.c_bytes};
+        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b};
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_cache.find(key);
         if (it != g_cache.end()) {
@@ -225,7 +224,7 @@ int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr) {
                       : gemm::neighbour_plan(p, &cfg, &split, &reduce) ? GEMM_PLAN_FROM_NEIGHBOUR
                       : GEMM_PLAN_FROM_MODEL;
     if (!forced) {
-        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b, p.c_bytes};
+        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b};
         std::lock_guard<std::mutex> lk(g_mu);
         if (g_cache.size() > 4096) g_cache.clear();
         g_cache.emplace(key, CachedPlan{pl, src});
@@ -240,7 +239,6 @@ int run(int32_t dtype, int32_t trans_b, int64_t M, int64_t N, int64_t K, const v
         int32_t epilogue = gemm::EPI_NONE, int32_t shift = 0, bool static_scratch = false) {
     Problem p{dtype, M, N, K, lda, ldb, ldc, uintptr_t(A), uintptr_t(B), uintptr_t(C), trans_b};
     const int64_t c_esize = epilogue == gemm::EPI_I8 ? 1 : (epilogue == gemm::EPI_NONE ? 4 : 2);
-    p.c_bytes = int32_t(c_esize);
     if (shift < 0 || shift > 31) return GEMM_ERR_INVALID_VALUE;
     int rc = validate(p, A, B, C, c_esize);
     if (rc != GEMM_OK) return rc;

@@ -100,13 +100,11 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
         const int64_t rows = std::min<int64_t>(c.bm, p.M), cols = std::min<int64_t>(c.bn, p.N);
         const double in_kernel_us = 2.5 + 0.35 * double(rows) +
                                     double(pl.split_k - 1) * double(rows * cols) * 4.0 / chip.wg_cold_bytes_per_s * 1e6;
-        
         int32_t mode = reduce >= 0 ? reduce
                      : p.dtype == DT_I8 ? ((c.family == FAM_RING || c.family == FAM_GEMV) ? REDUCE_ATOMIC_FLAG
                                                                                        : REDUCE_ATOMIC)
                      : (in_kernel_us <= chip.launch_us ? REDUCE_LAST_SLICE : REDUCE_SEPARATE);
-        if ((mode == REDUCE_ATOMIC || mode == REDUCE_ATOMIC_FLAG) && (p.dtype != DT_I8 || p.c_bytes != 4))
-            mode = REDUCE_SEPARATE;
+        if ((mode == REDUCE_ATOMIC || mode == REDUCE_ATOMIC_FLAG) && p.dtype != DT_I8) mode = REDUCE_SEPARATE;
         if (mode == REDUCE_ATOMIC_FLAG && c.family != FAM_RING && c.family != FAM_GEMV) mode = REDUCE_ATOMIC;
         pl.reduce_in_kernel = mode;
         // atomic with slice 0's zeros: their round trip, growing with the slices that add into
@@ -150,7 +148,7 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     // 128-column ones).
     const double b_line = (!p.trans_b && c.bn * e < 128) ? 128.0 / double(c.bn * e) : 1.0;
     const double a_bytes = double(p.M) * p.K * e, b_bytes = double(p.K) * p.N * e * b_line;
-    const double c_bytes = double(p.M) * p.N * p.c_bytes;
+    const double c_bytes = double(p.M) * p.N * 4;
     const double a_reads = a_bytes * double(pl.tiles_n);
     const double b_reads = b_bytes * double(pl.tiles_m);
     const double ws = partial_planes ? 2.0 * double(pl.workspace_bytes)

@@ -13,7 +13,6 @@ struct Problem {
     int64_t lda, ldb, ldc;
     uintptr_t a_addr, b_addr, c_addr;
     int32_t trans_b = 0;   // 1: B stored column-major (N x K, row stride ldb)
-    int32_t c_bytes = 4;   // bytes of an output: 4, or 1 or 2 of a narrowed one (never summed atomically)
 };
 
 struct Plan {

@@ -221,3 +221,14 @@ def test_bf16_infinities_and_nans_propagate(cfg):
     assert np.array_equal(nan_b, np.isnan(ref)), "bf16 NaN positions differ"
     ref_bits = oracle.get().round_bf16(ref)
     assert np.array_equal(Cb[~np.isnan(ref)], ref_bits[~np.isnan(ref)]), "bf16 non-NaN outputs differ"
+
+
+@pytest.mark.parametrize("M,N,K,bt", [(192, 1984, 2624, 1), (589, 771, 1647, 1), (3424, 128, 7680, 0)])
+def test_bf16_output_rounds_the_fp32_calls_result(M, N, K, bt):
+    """The library's own plans: gemm_bf16_bf16 is gemm_bf16_f32's result rounded, bit for bit
+    (the same K slices, so the same fp32 sums; sizes where a plan chosen by output width
+    split K otherwise)."""
+    A, B = inputs.make_inputs("bf16", M, N, K, seed=60)
+    Bx = np.ascontiguousarray(B.T) if bt else B
+    wide = g.gemm_gpu_bt(BF, A, Bx) if bt else g.gemm_gpu(BF, A, Bx)
+    assert np.array_equal(run_epilogue("bf16", A, Bx, bt=bool(bt)), inputs.bf16_bits_from_f32(wide))

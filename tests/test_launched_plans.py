@@ -1,0 +1,77 @@
+"""What the GEMM entry points launch, against what gemm_plan says (CPU only): the C ABI and
+the selector built host-only with tests/record_stub.cpp in place of the device side."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+from paper_2512_13282_amd import binding as b
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_2512_13282_amd", "csrc")
+I8, BF = b.GEMM_DTYPE_I8_I32, b.GEMM_DTYPE_BF16_F32
+FA, FB, FC = 1 << 40, 1 << 41, 3 << 40    # 16-byte aligned addresses, far apart (never dereferenced)
+FIELDS = ("config", "split_k", "k_chunk", "reduce", "grid", "epilogue", "static_scratch", "tiles")
+
+
+class Recorder:
+    def __init__(self, path):
+        self.lib = ctypes.CDLL(path)
+        self.lib.gemm_plan.argtypes = self.lib.gemm_plan_bt.argtypes = b.lib().gemm_plan.argtypes
+
+    def call(self, name, M, N, K, bt, a_off=0):
+        fn = getattr(self.lib, name + ("_bt" if bt else ""))
+        i64, p = ctypes.c_int64, ctypes.c_void_p
+        shift = [4] if name in ("gemm_i8_i8", "gemm_i8_i16") else []
+        fn.argtypes = [i64, i64, i64, p, i64, p, i64, p, i64] + [ctypes.c_int] * len(shift) + [p]
+        rc = fn(M, N, K, FA + a_off, max(K, 1), FB, max(K if bt else N, 1), FC, max(N, 1), *shift, None)
+        out = (i64 * 8)()
+        self.lib.recorded_launch(out)
+        return rc, dict(zip(FIELDS, out))
+
+    def plan(self, dtype, M, N, K, bt, a_off=0):
+        info = b.PlanInfo()
+        fn = self.lib.gemm_plan_bt if bt else self.lib.gemm_plan
+        rc = fn(dtype, M, N, K, max(K, 1), max(K if bt else N, 1), max(N, 1), FA + a_off, FB, FC, ctypes.byref(info))
+        assert rc == b.GEMM_OK
+        return info
+
+
+@pytest.fixture(scope="module")
+def rec(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("rec") / "libgemm_rec.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"),
+                    os.path.join(CSRC, "gemm_api.cpp"), os.path.join(CSRC, "selector.cpp"),
+                    os.path.join(HERE, "record_stub.cpp"), "-o", out], check=True, capture_output=True, text=True)
+    return Recorder(out)
+
+
+def _shapes(n, seed):
+    rng = random.Random(seed)
+    log = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))
+    for _ in range(n):
+        M, N, K = log(1, 8192), log(32, 14336), log(32, 14336)
+        if rng.random() < 0.7:
+            N, K = max(64, N // 64 * 64), max(64, K // 64 * 64)
+        yield M, N, K, rng.randint(0, 1)
+
+
+def test_plan_does_not_depend_on_the_output_type(rec):
+    """The narrowed calls run the tile, split and K slices of the int32 / fp32 call, which is
+    what gemm_plan reports: the fp32 sums that gemm_bf16_bf16 rounds are gemm_bf16_f32's."""
+    known = [(192, 1984, 2624, 1), (3424, 128, 7680, 0), (589, 771, 1647, 1), (128, 704, 6272, 1)]
+    same = ("config", "split_k", "k_chunk", "grid")
+    for M, N, K, bt in known + list(_shapes(300, 1)):
+        for dtype, wide, narrow in ((BF, "gemm_bf16_f32", ["gemm_bf16_bf16"]),
+                                    (I8, "gemm_i8_i32", ["gemm_i8_i8", "gemm_i8_i16"])):
+            p = rec.plan(dtype, M, N, K, bt)
+            rc, w = rec.call(wide, M, N, K, bt)
+            assert rc == b.GEMM_OK and [w[k] for k in same] == [p.config, p.split_k, p.k_chunk, p.grid]
+            for name in narrow:
+                rc, x = rec.call(name, M, N, K, bt)
+                assert rc == b.GEMM_OK and [x[k] for k in same] == [w[k] for k in same], (name, M, N, K, bt, x, w)
+                if x["split_k"] > 1:     # int32 sums added into C need an int32 C
+                    assert x["reduce"] == (w["reduce"] if w["reduce"] <= b.GEMM_REDUCE_LAST_SLICE else 0)
