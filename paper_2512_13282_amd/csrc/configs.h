@@ -107,6 +107,15 @@ constexpr TileConfig kConfigs[] = {
 };
 constexpr int32_t kNumConfigs = int32_t(sizeof(kConfigs) / sizeof(kConfigs[0]));
 
+// The element-wise kernel (rows of under 16 bytes, strides past 4 MiB) that configurations 0
+// and 1 run in place of the 16-byte loader: workgroups its registers allow on a CU, and what
+// it sustains, as kConfigs says it of the loader.
+struct ElementKernel {
+    int32_t occupancy;
+    double  eff_i8, eff_bf16;
+};
+constexpr ElementKernel kElementKernels[2] = {{2, 0.05, 0.07}, {1, 0.07, 0.10}};
+
 // LDS bytes of one workgroup: `stages` copies of an A stage (bm x 128 B) and a
 // B stage (bn x 128 B).  The analog of the paper's L1 budget (Eq. 5) without
 // the C term: the output tile lives in registers, not in LDS.

@@ -113,6 +113,13 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
                : mode == REDUCE_ATOMIC_FLAG ? chip.flag_us * (1.0 + double(pl.split_k) / 8.0)
                : mode == REDUCE_ATOMIC ? chip.fill_us : chip.separate_us;
     }
+    // Configurations 0 and 1 run the element-wise kernel where the 16-byte loader cannot, and are
+    // then priced as that kernel: its occupancy and rates, whole rounds of workgroups, 5 us for
+    // every launch.  Over 157 such calls timed at every split the choice runs 1.01 times the best
+    // (priced as the loader, 1.09: half as many slices, bf16 8192 x 7 x 8192 204 us against 127).
+    const bool element =
+        cfg < 2 && c.family == FAM_GENERIC && !wide_rows_ok(p.dtype, p.trans_b, p.N, p.K, p.lda, p.ldb);
+    if (element && pl.split_k > 1 && pl.reduce_in_kernel != REDUCE_LAST_SLICE) red_us = chip.launch_us;
     const bool partial_planes =
         pl.split_k > 1 && pl.reduce_in_kernel != REDUCE_ATOMIC && pl.reduce_in_kernel != REDUCE_ATOMIC_FLAG;
     pl.workspace_bytes = partial_planes ? int64_t(pl.split_k) * p.M * p.N * 4 : 0;
@@ -120,24 +127,27 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     // Compute: whole rounds of resident workgroups (wave quantization).
     const double ops_clk = p.dtype == DT_I8 ? chip.i8_ops_per_clk_cu : chip.bf16_ops_per_clk_cu;
     const double cu_rate = ops_clk * chip.clock_hz;                 // ops/s per CU
-    const int64_t slots = int64_t(chip.cus) * c.occupancy;
+    const int32_t occupancy = element ? kElementKernels[cfg].occupancy : c.occupancy;
+    const int64_t slots = int64_t(chip.cus) * occupancy;
     const int64_t rounds = ceil_div(pl.grid, slots);
     const double wg_ops = 2.0 * c.bm * c.bn * double(pl.k_chunk);
-    const double eff = p.dtype == DT_I8 ? c.eff_i8 : c.eff_bf16;
-    const double wg_s = wg_ops / (cu_rate * eff / c.occupancy);
+    const double eff = element ? (p.dtype == DT_I8 ? kElementKernels[cfg].eff_i8 : kElementKernels[cfg].eff_bf16)
+                               : (p.dtype == DT_I8 ? c.eff_i8 : c.eff_bf16);
+    const double wg_s = wg_ops / (cu_rate * eff / occupancy);
     // A CU's resident workgroups share its rate, so the last round costs what it leaves on the
     // fullest CU (at least the time of one workgroup alone).
     const bool generic = c.family == FAM_GENERIC;
     const int64_t full = pl.grid / slots, last = pl.grid % slots;
-    const double resident = last ? double(std::min<int64_t>(c.occupancy, ceil_div(last, chip.cus))) : 0.0;
-    const double solo = (generic ? chip.generic_solo : chip.solo) * c.occupancy;
-    const double units = double(full * c.occupancy) + (last ? std::max(resident, c.occupancy > 1 ? solo : 1.0) : 0.0);
-    pl.t_comp_us = units * wg_s / c.occupancy * 1e6;
+    const double resident = last ? double(std::min<int64_t>(occupancy, ceil_div(last, chip.cus))) : 0.0;
+    const double solo = (generic ? chip.generic_solo : chip.solo) * occupancy;
+    const double units = double(full * occupancy) + (last ? std::max(resident, occupancy > 1 ? solo : 1.0) : 0.0);
+    pl.t_comp_us = (element ? double(rounds) * wg_s : units * wg_s / occupancy) * 1e6;
     // Each workgroup's prologue and epilogue, which the K loop does not hide.
     const double overhead_us =
-        (double(full * c.occupancy) + resident) *
-        ((generic ? chip.generic_us_per_kilo_output : chip.us_per_kilo_output) * double(c.bm * c.bn) / 1024.0 +
-         (generic ? chip.generic_us_per_workgroup : chip.us_per_workgroup));
+        element ? double(rounds) * chip.element_round_us / occupancy
+                : (double(full * occupancy) + resident) *
+                      ((generic ? chip.generic_us_per_kilo_output : chip.us_per_kilo_output) * double(c.bm * c.bn) / 1024.0 +
+                       (generic ? chip.generic_us_per_workgroup : chip.us_per_workgroup));
 
     // Memory: compulsory traffic at HBM speed; tile re-reads (Eqs. 6-7 analog)
     // mostly from L2/MALL; split-K partials written and read back once, or added
@@ -154,8 +164,9 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     const double ws = partial_planes ? 2.0 * double(pl.workspace_bytes)
                                      : (pl.split_k > 1 ? double(pl.split_k + 1) * p.M * p.N * 4 : 0.0);
     pl.traffic_bytes = a_reads + b_reads + c_bytes + ws;
-    pl.t_mem_us = ((a_bytes + b_bytes + c_bytes + ws) / chip.hbm_bytes_per_s +
-                   (a_reads + b_reads - a_bytes - b_bytes) / chip.reread_bytes_per_s) * 1e6;
+    const double hbm = element ? chip.element_hbm_bytes_per_s : chip.hbm_bytes_per_s;
+    const double reread = element ? chip.element_reread_bytes_per_s : chip.reread_bytes_per_s;
+    pl.t_mem_us = ((a_bytes + b_bytes + c_bytes + ws) / hbm + (a_reads + b_reads - a_bytes - b_bytes) / reread) * 1e6;
     // With one tile row every workgroup streams a strip of B of its own from HBM, beside
     // its slice of A, at a rate one workgroup's loads in flight bound: too few workgroups
     // cannot reach the HBM rate (measured: 112 unsplit workgroups of 32 x 128 at M = 16
@@ -166,7 +177,7 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
         pl.t_mem_us = std::max(pl.t_mem_us, double(rounds) * wg_bytes / chip.wg_cold_bytes_per_s * 1e6);
     }
 
-    pl.t_total_us = std::max(pl.t_comp_us, pl.t_mem_us) + overhead_us + chip.base_us + red_us;
+    pl.t_total_us = std::max(pl.t_comp_us, pl.t_mem_us) + overhead_us + (element ? chip.launch_us : chip.base_us) + red_us;
     return pl;
 }
 

@@ -48,6 +48,10 @@ struct Chip {
     // Time of a workgroup alone on a CU over that of a full CU's workgroups, each: latency-bound
     // GENERIC loops speed up least.
     double  solo = 0.178, generic_solo = 0.263;
+    // The element-wise kernel: the rates of compulsory traffic and of re-reads, and a round of
+    // workgroups' first loads and C stores.
+    double  element_hbm_bytes_per_s = 4.0e12, element_reread_bytes_per_s = 16.0e12;
+    double  element_round_us = 2.0;
     // Prologue and C stores of a workgroup: per 1024 outputs of its tile, and each.
     double  us_per_kilo_output = 0.216, generic_us_per_kilo_output = 0.194;
     double  us_per_workgroup = 0.474, generic_us_per_workgroup = 0.166;

@@ -366,3 +366,16 @@ def test_cached_plans_follow_strides(dtype):
     assert b.gemm_plan(dtype, M, N, K, K, N, N, AL, 2 * AL, 3 * AL) == near
     check_invariants(near, dtype, M, N, K)
     check_invariants(far, dtype, M, N, K)
+
+
+@pytest.mark.parametrize("dtype,M,N,K,lda,config,split", [
+    (BF, 2048, 1, 4096, 4096, 0, 16), (I8, 2048, 1, 4096, 4096, 0, 16), (BF, 8192, 7, 8192, 8192, 0, 4),
+    (BF, 4096, 5, 1000, 1000, 0, 8), (I8, 4096, 10, 4096, 4096, 0, 8), (I8, 1024, 15, 16384, 16384, 0, 32),
+    (BF, 1024, 1024, 1024, (1 << 21) + 64, 0, 2), (BF, 128, 2, 8192, 8192, 0, 64)])
+def test_element_wise_calls_are_priced_as_their_kernel(dtype, M, N, K, lda, config, split):
+    """Rows of under 16 bytes or strides past 4 MiB run the element-wise kernel: the splits
+    that fill the chip at its two workgroups to a compute unit (with the 16-byte loader's
+    four in the price, half as many, 1.2-1.6 times the time)."""
+    p = plan(dtype, M, N, K, lda=lda)
+    check_invariants(p, dtype, M, N, K)
+    assert (p["config"], p["split_k"]) == (config, split), p["name"]
