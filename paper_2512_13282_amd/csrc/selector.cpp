@@ -80,6 +80,13 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     }
     pl.grid = pl.tiles_m * pl.tiles_n * pl.split_k;
 
+    // Configurations 0 and 1 run the element-wise kernel where the 16-byte loader cannot, and are
+    // then priced as that kernel: its occupancy and rates, whole rounds of workgroups, 5 us for
+    // every launch.  Over 157 such calls timed at every split the choice runs 1.01 times the best
+    // (priced as the loader, 1.09: half as many slices, bf16 8192 x 7 x 8192 204 us against 127).
+    const bool element =
+        cfg < 2 && c.family == FAM_GENERIC && !wide_rows_ok(p.dtype, p.trans_b, p.N, p.K, p.lda, p.ldb);
+
     // Split-K reduction (REDUCE_* in launch.h).  Last slice: the last slice of each
     // tile reads the tile's partials, sixteen slices per round trip of 256 threads x 4
     // columns, at the end of the kernel.  Separate: one more launch streaming the
@@ -96,30 +103,30 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
         // kernel by 1-2 us at M = 1 and loses by 3-7 us at M = 16 (10-40 us at M = 64):
         // beside its three dependent round trips it issues the tile's device-coherent
         // partial stores, which grow with the tile's valid rows, and one workgroup reads
-        // every other slice's partial tile.  The separate kernel is priced as a launch.
+        // every other slice's partial tile.  The estimate decides between the two by a line of
+        // its own, above the separate kernel's fitted price: over 295 pairs timed at M = 1 to 7
+        // the last slice's sum is 0.3-0.5 us the faster below 3.9 us, the separate kernel by as
+        // much from there to 5 and by 1.5 us past it; but with 12 or 16 slices at M = 2 and 3 the
+        // last slice's is still 4-12 % the faster between 3.6 and 5.
         const int64_t rows = std::min<int64_t>(c.bm, p.M), cols = std::min<int64_t>(c.bn, p.N);
         const double in_kernel_us = 2.5 + 0.35 * double(rows) +
                                     double(pl.split_k - 1) * double(rows * cols) * 4.0 / chip.wg_cold_bytes_per_s * 1e6;
         int32_t mode = reduce >= 0 ? reduce
                      : p.dtype == DT_I8 ? ((c.family == FAM_RING || c.family == FAM_GEMV) ? REDUCE_ATOMIC_FLAG
                                                                                        : REDUCE_ATOMIC)
-                     : (in_kernel_us <= chip.launch_us ? REDUCE_LAST_SLICE : REDUCE_SEPARATE);
+                     : (in_kernel_us <= chip.last_slice_below_us ? REDUCE_LAST_SLICE : REDUCE_SEPARATE);
         if ((mode == REDUCE_ATOMIC || mode == REDUCE_ATOMIC_FLAG) && p.dtype != DT_I8) mode = REDUCE_SEPARATE;
         if (mode == REDUCE_ATOMIC_FLAG && c.family != FAM_RING && c.family != FAM_GEMV) mode = REDUCE_ATOMIC;
         pl.reduce_in_kernel = mode;
-        // atomic with slice 0's zeros: their round trip, growing with the slices that add into
-        // the same lines of C
+        // Atomic with slice 0's zeros: what the other slices wait for beyond their own work.  At
+        // 0.1 us the model split products of a few microseconds that run faster whole: int8
+        // 80 x 256 x 256 5.6 us in two slices, 4.6 in one (of 1122 int8 calls timed at their 15 or
+        // so likeliest plans 29 change at 0.4 us, to 0.90 of the time, one to more than 1.05).
         red_us = mode == REDUCE_LAST_SLICE ? in_kernel_us
-               : mode == REDUCE_ATOMIC_FLAG ? chip.flag_us * (1.0 + double(pl.split_k) / 8.0)
+               : mode == REDUCE_ATOMIC_FLAG ? chip.flag_us
+               : element ? chip.element_launch_us
                : mode == REDUCE_ATOMIC ? chip.fill_us : chip.separate_us;
     }
-    // Configurations 0 and 1 run the element-wise kernel where the 16-byte loader cannot, and are
-    // then priced as that kernel: its occupancy and rates, whole rounds of workgroups, 5 us for
-    // every launch.  Over 157 such calls timed at every split the choice runs 1.01 times the best
-    // (priced as the loader, 1.09: half as many slices, bf16 8192 x 7 x 8192 204 us against 127).
-    const bool element =
-        cfg < 2 && c.family == FAM_GENERIC && !wide_rows_ok(p.dtype, p.trans_b, p.N, p.K, p.lda, p.ldb);
-    if (element && pl.split_k > 1 && pl.reduce_in_kernel != REDUCE_LAST_SLICE) red_us = chip.launch_us;
     const bool partial_planes =
         pl.split_k > 1 && pl.reduce_in_kernel != REDUCE_ATOMIC && pl.reduce_in_kernel != REDUCE_ATOMIC_FLAG;
     pl.workspace_bytes = partial_planes ? int64_t(pl.split_k) * p.M * p.N * 4 : 0;
@@ -135,13 +142,14 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
                                : (p.dtype == DT_I8 ? c.eff_i8 : c.eff_bf16);
     const double wg_s = wg_ops / (cu_rate * eff / occupancy);
     // A CU's resident workgroups share its rate, so the last round costs what it leaves on the
-    // fullest CU (at least the time of one workgroup alone).
+    // fullest CU.  A workgroup alone then runs at a full CU's rate, which is how the timed calls
+    // lie (charged a fifth or half more where two fit, the choice is 1.092 and 1.10 times the best
+    // in place of 1.086), but for the small GENERIC tiles.
     const bool generic = c.family == FAM_GENERIC;
     const int64_t full = pl.grid / slots, last = pl.grid % slots;
     const double resident = last ? double(std::min<int64_t>(occupancy, ceil_div(last, chip.cus))) : 0.0;
-    const double solo = (generic ? chip.generic_solo : chip.solo) * occupancy;
-    const double units = double(full * occupancy) + (last ? std::max(resident, occupancy > 1 ? solo : 1.0) : 0.0);
-    pl.t_comp_us = (element ? double(rounds) * wg_s : units * wg_s / occupancy) * 1e6;
+    const double units = std::max(resident, generic && occupancy == 4 && last ? chip.generic_solo : 0.0);
+    pl.t_comp_us = (element ? double(rounds) : double(full) + units / occupancy) * wg_s * 1e6;
     // Each workgroup's prologue and epilogue, which the K loop does not hide.
     const double overhead_us =
         element ? double(rounds) * chip.element_round_us / occupancy
@@ -177,7 +185,7 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
         pl.t_mem_us = std::max(pl.t_mem_us, double(rounds) * wg_bytes / chip.wg_cold_bytes_per_s * 1e6);
     }
 
-    pl.t_total_us = std::max(pl.t_comp_us, pl.t_mem_us) + overhead_us + (element ? chip.launch_us : chip.base_us) + red_us;
+    pl.t_total_us = std::max(pl.t_comp_us, pl.t_mem_us) + overhead_us + (element ? chip.element_launch_us : chip.base_us) + red_us;
     return pl;
 }
 

@@ -40,18 +40,17 @@ struct Chip {
     double  reread_bytes_per_s = 19.8e12;   // A/B tile re-reads mostly served by L2/MALL
     double  wg_cold_bytes_per_s = 31.2e9;  // one workgroup streaming its own strip of B (its loads
                                           // in flight over the latency)
-    double  launch_us = 5.0;              // a launch on the stream, as the split-K reductions are chosen by it
-    double  base_us = 0.367;               // of every plan
-    double  separate_us = 3.61;          // split-K: the separate reduction's launch ...
-    double  fill_us = 2.89;             // ... the fill kernel's ahead of atomic adds ...
-    double  flag_us = 0.0994;             // ... and C zeroed by the first slice, times 1 + split / 8
-    // Time of a workgroup alone on a CU over that of a full CU's workgroups, each: latency-bound
-    // GENERIC loops speed up least.
-    double  solo = 0.178, generic_solo = 0.263;
-    // The element-wise kernel: the rates of compulsory traffic and of re-reads, and a round of
-    // workgroups' first loads and C stores.
+    double  base_us = 0.367;              // of every plan
+    double  separate_us = 3.61;           // split-K: the separate reduction's launch ...
+    double  fill_us = 2.89;               // ... the fill kernel's ahead of atomic adds ...
+    double  flag_us = 0.4;                // ... and waiting for the first slice's zeros
+    double  last_slice_below_us = 5.0;    // largest estimate that the last slice's own sum is taken at
+    // The element-wise kernel: the rates of compulsory traffic and of re-reads, a round of
+    // workgroups' first loads and C stores, and a launch, its own or beside it.
     double  element_hbm_bytes_per_s = 4.0e12, element_reread_bytes_per_s = 16.0e12;
-    double  element_round_us = 2.0;
+    double  element_round_us = 2.0, element_launch_us = 5.0;
+    // A GENERIC workgroup alone on a CU that holds four runs at this much under the full CU's rate.
+    double  generic_solo = 1.05;
     // Prologue and C stores of a workgroup: per 1024 outputs of its tile, and each.
     double  us_per_kilo_output = 0.216, generic_us_per_kilo_output = 0.194;
     double  us_per_workgroup = 0.474, generic_us_per_workgroup = 0.166;

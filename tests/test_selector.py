@@ -379,3 +379,11 @@ def test_element_wise_calls_are_priced_as_their_kernel(dtype, M, N, K, lda, conf
     p = plan(dtype, M, N, K, lda=lda)
     check_invariants(p, dtype, M, N, K)
     assert (p["config"], p["split_k"]) == (config, split), p["name"]
+
+
+def test_small_int8_products_run_whole():
+    """A second K slice costs these products more than it saves (4.2-4.6 us whole, 5.1-5.6 split)."""
+    for M, N, K in ((80, 256, 256), (300, 256, 256), (144, 384, 256)):
+        assert plan(I8, M, N, K)["split_k"] == 1, (M, N, K)
+    assert plan_bt(I8, 1, 1984, 2368)["split_k"] == 1
+    assert plan_bt(I8, 1, 2112, 9856)["split_k"] == 2      # 7.8 us, 10.0 whole
