@@ -50,8 +50,8 @@
  *                           makes every workspace allocation fail this way (a
  *                           test hook; read at each allocation).
  *   GEMM_ERR_HIP            a HIP launch/runtime error.
- *   GEMM_ERR_SCRATCH_LIMIT  (gemm_bf16_f32_noalloc only) the plan's split-K
- *                           partials exceed its fixed scratch.
+ *   GEMM_ERR_SCRATCH_LIMIT  (gemm_bf16_f32_noalloc only) a forced or loaded plan's
+ *                           split-K partials or counters exceed its fixed scratch.
  * M == 0 or N == 0 is a successful no-op.  K == 0 writes zeros (empty sum).
  * Pointers or strides that are not 16-byte aligned are accepted and routed to
  * an alignment-agnostic kernel (slower, same result).
@@ -168,16 +168,17 @@ int gemm_bf16_f32(int64_t M, int64_t N, int64_t K,
 
 /* For callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): gemm_bf16_f32 with the
- * same arguments, plan and result (bit for bit: the same kernels sum in the same
- * order), except that a split-K plan keeps its partial sums and per-tile arrival
+ * same arguments, where a split-K plan keeps its partial sums and per-tile arrival
  * counters in a fixed 16 MiB array of device memory that the library holds for
  * each GPU it runs on until the process ends (64 KiB of counters, the rest for
  * partials: split_k * M * N * 4 bytes must fit in 16 MiB - 64 KiB).  It never
  * calls hipMalloc, hipFree or an allocating library routine; the counters are
- * cleared by a fill kernel on `stream` at each split-K call.  Where the partials
- * of the library's own plan do not fit, the same configuration runs unsplit; a
- * plan that was forced or loaded from a file and does not fit returns
- * GEMM_ERR_SCRATCH_LIMIT before anything is queued.
+ * cleared by a fill kernel on `stream` at each split-K call.  Where the plan that
+ * gemm_plan reports fits the array, it runs, with gemm_bf16_f32's result bit for
+ * bit (the same kernels sum in the same order).  Where it does not, the best plan
+ * that fits runs, split otherwise or not at all: a result of the same precision,
+ * its fp32 sums taken in another order.  A plan that was forced or loaded from a
+ * file and does not fit returns GEMM_ERR_SCRATCH_LIMIT before anything is queued.
  * Every call on one GPU shares that GPU's array: calls that overlap in time on
  * one GPU (different streams, or host threads) race on it and must not be
  * issued; calls queued in order on one stream are safe.  Other errors as

@@ -39,8 +39,10 @@ struct Key {
     int64_t M, N, K;
     int32_t align;     // alignment_class
     int32_t trans_b;
+    int32_t fixed_scratch;
     bool operator==(const Key &o) const {
-        return dtype == o.dtype && M == o.M && N == o.N && K == o.K && align == o.align && trans_b == o.trans_b;
+        return dtype == o.dtype && M == o.M && N == o.N && K == o.K && align == o.align && trans_b == o.trans_b &&
+               fixed_scratch == o.fixed_scratch;
     }
 };
 // 64-bit FNV-1a over the key's fields (its published offset basis and prime).
@@ -49,7 +51,7 @@ struct KeyHash {
         uint64_t h = 1469598103934665603ULL;
         auto mix = [&](uint64_t v) { h = (h ^ v) * 1099511628211ULL; };
         mix(uint64_t(k.dtype)); mix(uint64_t(k.M)); mix(uint64_t(k.N)); mix(uint64_t(k.K));
-        mix(uint64_t(k.align)); mix(uint64_t(k.trans_b));
+        mix(uint64_t(k.align)); mix(uint64_t(k.trans_b)); mix(uint64_t(k.fixed_scratch));
         return size_t(h);
     }
 };
@@ -70,7 +72,7 @@ struct Shape {
     }
 };
 struct ShapeHash {
-    size_t operator()(const Shape &s) const { return KeyHash()(Key{s.dtype, s.M, s.N, s.K, 0, s.trans_b}); }
+    size_t operator()(const Shape &s) const { return KeyHash()(Key{s.dtype, s.M, s.N, s.K, 0, s.trans_b, 0}); }
 };
 struct LoadedPlan {
     int32_t config, split, reduce;
@@ -181,8 +183,11 @@ int validate(const Problem &p, const void *A, const void *B, const void *C, int6
     return GEMM_OK;
 }
 
-// The plan for a call, and where it came from (GEMM_PLAN_FROM_*) if `source` is given.
-int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr) {
+// The plan for a call, and where it came from (GEMM_PLAN_FROM_*) if `source` is given.  With
+// fixed_scratch a plan that the library chooses fits the fixed scratch; one that the caller
+// asked for (forced, or from a plan file) is left as it is, and launch_gemm refuses it if it
+// does not fit.
+int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr, bool fixed_scratch = false) {
     std::call_once(g_env_once, load_env_plans);
     Override ov;
     {
@@ -191,7 +196,7 @@ int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr) {
     }
     const bool forced = ov.family >= 0 || ov.config >= 0 || ov.split > 0 || ov.reduce >= 0;
     if (!forced) {
-        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b};
+        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b, fixed_scratch};
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_cache.find(key);
         if (it != g_cache.end()) {
@@ -214,7 +219,8 @@ int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr) {
         loaded = loaded && gemm::config_applicable(p, lp.config);
         if (loaded) pl = gemm::evaluate(p, lp.config, lp.split, gemm::Chip(), lp.reduce);
     }
-    if (!loaded && !gemm::select_plan(p, &pl, ov.family, ov.config, ov.split, gemm::Chip(), ov.reduce))
+    if (!loaded && !gemm::select_plan(p, &pl, ov.family, ov.config, ov.split, gemm::Chip(), ov.reduce,
+                                      fixed_scratch && !forced))
         return GEMM_ERR_UNSUPPORTED;
     // select_plan consults the compiled table, then the nearest-M neighbours, then the model.
     int32_t cfg, split, reduce;
@@ -224,7 +230,7 @@ int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr) {
                       : gemm::neighbour_plan(p, &cfg, &split, &reduce) ? GEMM_PLAN_FROM_NEIGHBOUR
                       : GEMM_PLAN_FROM_MODEL;
     if (!forced) {
-        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b};
+        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b, fixed_scratch};
         std::lock_guard<std::mutex> lk(g_mu);
         if (g_cache.size() > 4096) g_cache.clear();
         g_cache.emplace(key, CachedPlan{pl, src});
@@ -244,15 +250,8 @@ int run(int32_t dtype, int32_t trans_b, int64_t M, int64_t N, int64_t K, const v
     if (rc != GEMM_OK) return rc;
     if (M == 0 || N == 0) return GEMM_OK;
     Plan pl;
-    int32_t source = GEMM_PLAN_FROM_MODEL;
-    rc = plan_for(p, &pl, &source);
+    rc = plan_for(p, &pl, nullptr, static_scratch);
     if (rc != GEMM_OK) return rc;
-    // Without allocation, a split that the library chose itself and whose partials exceed the
-    // fixed scratch gives way to the same configuration unsplit; one that the caller asked for
-    // (forced, or from a plan file) is refused by launch_gemm.
-    const bool own = source != GEMM_PLAN_FROM_FORCED && source != GEMM_PLAN_FROM_FILE;
-    if (static_scratch && own && pl.workspace_bytes > gemm::kStaticScratchBytes - gemm::kScratchCounterBytes)
-        pl = gemm::evaluate(p, pl.config, 1);
 
     gemm::KernelArgs a{};
     a.dtype = dtype;

@@ -245,14 +245,19 @@ bool neighbour_plan(const Problem &p, int32_t *config, int32_t *split, int32_t *
     return true;
 }
 
+bool fits_fixed_scratch(const Plan &pl) {
+    const int64_t counters = pl.split_k > 1 && pl.reduce_in_kernel == REDUCE_LAST_SLICE ? pl.tiles_m * pl.tiles_n : 0;
+    return pl.workspace_bytes <= kStaticScratchBytes - kScratchCounterBytes && counters * 4 <= kScratchCounterBytes;
+}
+
 bool select_plan(const Problem &p, Plan *out, int32_t forced_family, int32_t forced_config,
-                 int32_t forced_split, const Chip &chip, int32_t forced_reduce) {
+                 int32_t forced_split, const Chip &chip, int32_t forced_reduce, bool fixed_scratch) {
     static const int32_t kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
     if (forced_family < 0 && forced_config < 0 && forced_split <= 0 && forced_reduce < 0) {
         int32_t cfg, split, reduce;
         if (tuned_plan(p, &cfg, &split, &reduce) || neighbour_plan(p, &cfg, &split, &reduce)) {
             *out = evaluate(p, cfg, split, chip, reduce);
-            return true;
+            if (!fixed_scratch || fits_fixed_scratch(*out)) return true;
         }
     }
     bool found = false;
@@ -278,6 +283,7 @@ bool select_plan(const Problem &p, Plan *out, int32_t forced_family, int32_t for
             const int32_t split = forced_split > 0 ? forced_split : s;
             Plan pl = evaluate(p, cfg, split, chip, forced_reduce);
             if (forced_split <= 0 && pl.split_k != split) continue;   // duplicate of a smaller split
+            if (fixed_scratch && !fits_fixed_scratch(pl)) continue;
             // Ties (memory-bound shapes, where every tile of one size moves the same
             // bytes) go to the plan with the shorter compute time: the faster kernel.
             const bool tie = found && std::abs(pl.t_total_us - best.t_total_us) <= 1e-9 * best.t_total_us;

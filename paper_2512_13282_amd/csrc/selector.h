@@ -90,8 +90,12 @@ bool neighbour_plan(const Problem &p, int32_t *config, int32_t *split, int32_t *
 // >= 0 pins the configuration; forced_split > 0 pins the split factor.
 // Returns false if nothing applicable exists (only possible when forced).
 // forced_reduce >= 0 pins the split-K reduction (0 separate kernel, 1 in-kernel).
+// fixed_scratch: the best plan that fits_fixed_scratch (an unsplit one always does).
 bool select_plan(const Problem &p, Plan *out, int32_t forced_family = -1,
                  int32_t forced_config = -1, int32_t forced_split = 0,
-                 const Chip &chip = Chip(), int32_t forced_reduce = -1);
+                 const Chip &chip = Chip(), int32_t forced_reduce = -1, bool fixed_scratch = false);
+
+// Whether a plan's split-K partials and counters fit the fixed scratch (launch.h).
+bool fits_fixed_scratch(const Plan &pl);
 
 }  // namespace gemm

@@ -1,6 +1,6 @@
 """gemm_bf16_f32_noalloc where the library's own split-K plan does not fit its fixed scratch:
-the call runs unsplit and exact (integer-valued operands), while the same split asked for by
-force is refused with nothing written (needs an MI355X)."""
+the call runs the best plan that fits and is exact (integer-valued operands), while the same
+split asked for by force is refused with nothing written (needs an MI355X)."""
 import numpy as np
 import pytest
 import torch

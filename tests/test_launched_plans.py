@@ -75,3 +75,34 @@ def test_plan_does_not_depend_on_the_output_type(rec):
                 assert rc == b.GEMM_OK and [x[k] for k in same] == [w[k] for k in same], (name, M, N, K, bt, x, w)
                 if x["split_k"] > 1:     # int32 sums added into C need an int32 C
                     assert x["reduce"] == (w["reduce"] if w["reduce"] <= b.GEMM_REDUCE_LAST_SLICE else 0)
+
+
+LIMIT = (16 << 20) - (64 << 10)
+
+
+def test_noalloc_runs_the_best_plan_that_fits(rec):
+    """gemm_bf16_f32_noalloc runs gemm_bf16_f32's plan where its partials fit the fixed scratch,
+    else one chosen with the scratch as a bound: not the tile of the split plan on the few
+    compute units that it fills unsplit."""
+    changed = 0
+    for M, N, K, _ in list(_shapes(400, 2)):
+        p = rec.plan(BF, M, N, K, 0)
+        rc, x = rec.call("gemm_bf16_f32_noalloc", M, N, K, 0)
+        assert rc == b.GEMM_OK and x["static_scratch"] == 1
+        planes = x["split_k"] * M * N * 4 if x["split_k"] > 1 else 0
+        assert planes <= LIMIT and (x["reduce"] != b.GEMM_REDUCE_LAST_SLICE or x["tiles"] * 4 <= 64 << 10)
+        if p.workspace_bytes <= LIMIT:
+            assert [x[k] for k in ("config", "split_k", "k_chunk")] == [p.config, p.split_k, p.k_chunk]
+        else:
+            changed += 1
+    assert changed >= 5
+
+
+@pytest.mark.parametrize("M,N,K", [(1504, 1408, 2880), (196, 2833, 7273), (330, 2555, 9583), (1200, 1792, 3136),
+                                   (512, 8192, 8192), (2048, 4096, 14336), (256, 13824, 5120)])
+def test_noalloc_fallback_fills_the_chip(rec, M, N, K):
+    """Calls whose split plan does not fit: 23 to 128 workgroups if that plan's tile ran
+    unsplit, on 256 compute units (1.1-3.8 times the time of the plans below)."""
+    assert rec.plan(BF, M, N, K, 0).workspace_bytes > LIMIT
+    rc, x = rec.call("gemm_bf16_f32_noalloc", M, N, K, 0)
+    assert rc == b.GEMM_OK and x["grid"] >= 130, x
