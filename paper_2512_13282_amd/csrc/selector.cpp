@@ -43,12 +43,8 @@ bool vector_loads_ok(const Problem &p) {
 }
 
 int32_t alignment_class(const Problem &p) {
-    const int64_t e = elem_bytes(p.dtype);
-    const bool a_ok = p.a_addr % 16 == 0 && (p.lda * e) % 16 == 0 && (p.K * e) % 16 == 0;
-    const bool b_ok = p.b_addr % 16 == 0 && (p.ldb * e) % 16 == 0 && ((p.trans_b ? p.K : p.N) * e) % 16 == 0;
     return (vector_loads_ok(p) ? ALIGN_VECTOR : 0) |
-           (wide_rows_ok(p.dtype, p.trans_b, p.N, p.K, p.lda, p.ldb) ? ALIGN_WIDE : 0) | (a_ok ? ALIGN_A : 0) |
-           (b_ok ? ALIGN_B : 0);
+           (wide_rows_ok(p.dtype, p.trans_b, p.N, p.K, p.lda, p.ldb) ? ALIGN_WIDE : 0);
 }
 
 bool config_applicable(const Problem &p, int32_t cfg) {

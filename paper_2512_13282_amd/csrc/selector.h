@@ -64,7 +64,7 @@ bool vector_loads_ok(const Problem &p);
 
 // What a call's addresses and strides allow, as bits: everything a plan depends on beside
 // dtype, sizes and B's layout (plans are cached by both).
-enum : int32_t { ALIGN_VECTOR = 1, ALIGN_WIDE = 2, ALIGN_A = 4, ALIGN_B = 8 };
+enum : int32_t { ALIGN_VECTOR = 1, ALIGN_WIDE = 2 };
 int32_t alignment_class(const Problem &p);
 
 // Whether config `cfg` can run problem `p` at all.
