@@ -55,7 +55,8 @@ constexpr int32_t kSlotKBytes = 64;
 // Family DIRECT: both operands stream global -> LDS directly (buffer loads with
 // an LDS destination); B's fragments come from LDS transpose reads, or, for B
 // stored column-major, from 16-byte reads like A's.  The ping-pong kernel has two rows:
-// 13, row-major B only (plan files name configurations by index), and 44, both layouts.
+// 44, both layouts, and kPingPongRowOnly, row-major B only, for plan files and forced plans
+// that name it (by index); the selector's own choice passes it by.
 constexpr TileConfig kConfigs[] = {
     // family       bm   bn  wm wn occ stages eff_i8 eff_bf16 colB name
     {FAM_GENERIC,   64,  64, 2, 2, 4, 2, 0.141, 0.156, 1, "generic_64x64_w4"},
@@ -71,7 +72,7 @@ constexpr TileConfig kConfigs[] = {
     {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.640, 0.674, 1, "direct_256x256_w8"},
     {FAM_DIRECT,   256, 256, 4, 2, 1, 2, 0.608, 0.694, 1, "direct_256x256_w8t"},
     {FAM_DIRECT,   128, 256, 2, 4, 1, 2, 0.457, 0.388, 1, "direct_128x256_w8"},
-    {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.778, 0.766, 0, "pingpong_256x256_w8"},
+    {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.779, 0.767, 0, "pingpong_256x256_w8"},
     {FAM_SKINNY,    32, 256, 1, 4, 1, 4, 0.128, 0.144, 0, "stream_32x256_s4"},
     {FAM_SKINNY,    64, 256, 1, 4, 1, 3, 0.215, 0.285, 0, "stream_64x256_s3"},
     {FAM_RING,     256, 256, 2, 4, 1, 4, 0.684, 0.662, 1, "ring_256x256_w8"},
@@ -105,6 +106,7 @@ constexpr TileConfig kConfigs[] = {
     {FAM_DIRECT,   256, 256, 2, 4, 1, 2, 0.779, 0.767, 1, "quad_256x256_w8"},
     {FAM_DIRECT,    64,  64, 2, 2, 3, 3, 0.130, 0.150, 1, "direct_64x64_w4_s3"},
 };
+constexpr int32_t kPingPongRowOnly = 13;
 constexpr int32_t kNumConfigs = int32_t(sizeof(kConfigs) / sizeof(kConfigs[0]));
 
 // The element-wise kernel (rows of under 16 bytes, strides past 4 MiB) that configurations 0

@@ -262,6 +262,7 @@ bool select_plan(const Problem &p, Plan *out, int32_t forced_family, int32_t for
         if (forced_config >= 0 && cfg != forced_config) continue;
         if (forced_family >= 0 && kConfigs[cfg].family != forced_family) continue;
         if (!config_applicable(p, cfg)) continue;
+        if (forced_family < 0 && forced_config < 0 && cfg == kPingPongRowOnly) continue;   // 44 is the same kernel
         // Where vectorised kernels can run, GENERIC ones compete only for short K (rows of at
         // most 2 KiB), where a tile is mostly prologue and C stores and their small tiles (64
         // rows at most, up to four to a CU) win: bf16 25440 x 64 x 64 8.6 -> 4.6 us, int8 43840 x 64 x 128 9.2 -> 5.0 us.
