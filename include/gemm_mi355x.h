@@ -34,7 +34,11 @@
  * the same value while work of the old one is still running must not be used.
  *
  * Execution: every GEMM call is asynchronous on `stream` (a hipStream_t passed
- * as void*; NULL = the null stream) and never synchronizes the device.
+ * as void*; NULL = the null stream) and never synchronizes the device.  A call
+ * may be captured into a HIP graph.  The workspace does not grow in a capture: a
+ * call whose split-K plan needs more than `stream` holds then runs the best plan
+ * without a split (a forced or loaded plan is left as it is), so run it once on
+ * the stream beforehand if the captured call is to split K too.
  *
  * Errors: every entry point returns an int status (gemm_status_t) and never
  * throws or aborts.  Argument checks run on the host BEFORE any HIP call:

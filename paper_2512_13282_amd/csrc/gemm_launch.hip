@@ -74,14 +74,18 @@ static bool fail_workspace_for_test() {
     return e != nullptr && e[0] == '1';
 }
 
-static int acquire_workspace(hipStream_t stream, size_t partial_bytes, int64_t counter_words, void **partials,
-                             uint32_t **counters) {
+static int acquire_workspace(hipStream_t stream, size_t partial_bytes, int64_t counter_words, bool grow_in_capture,
+                             void **partials, uint32_t **counters) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return LAUNCH_HIP_ERROR;
     std::lock_guard<std::mutex> lk(g_ws_mu);
     Workspace &w = g_ws[{dev, reinterpret_cast<uintptr_t>(stream)}];
-    if ((w.partial_bytes < partial_bytes || w.counter_cap < counter_words) && fail_workspace_for_test())
-        return LAUNCH_NO_MEMORY;
+    if (w.partial_bytes < partial_bytes || w.counter_cap < counter_words) {
+        if (fail_workspace_for_test()) return LAUNCH_NO_MEMORY;
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (!grow_in_capture && hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
+        if (capture == hipStreamCaptureStatusActive) return LAUNCH_CAPTURING;
+    }
     if (w.partial_bytes < partial_bytes) {
         if (w.partials != nullptr && hipFreeAsync(w.partials, stream) != hipSuccess) return LAUNCH_HIP_ERROR;
         w.partials = nullptr;
@@ -220,7 +224,8 @@ int launch_gemm(const KernelArgs &a, int32_t cfg, int64_t grid, void *stream_ptr
                 if (hipGetLastError() != hipSuccess) return LAUNCH_HIP_ERROR;
             }
         } else {
-            const int rc = acquire_workspace(stream, bytes, counter_words, &args.workspace, &args.counters);
+            const int rc = acquire_workspace(stream, bytes, counter_words, args.callers_plan != 0, &args.workspace,
+                                             &args.counters);
             if (rc != LAUNCH_OK) return rc;
         }
     }

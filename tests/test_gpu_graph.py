@@ -120,3 +120,42 @@ def test_graph_replays_noalloc():
         torch.cuda.synchronize()
         got = dC.cpu().numpy()[: M * ldc].reshape(M, ldc)[:, :N]
         assert np.array_equal(got.view(np.uint32), eager.view(np.uint32)), f"replay {rep} differs"
+
+
+@pytest.mark.parametrize("dtype", [I8, BF], ids=["i8", "bf16"])
+def test_capture_without_a_workspace_allocates_nothing(dtype):
+    """A call whose own plan splits K, captured on a stream that holds no workspace yet: it runs
+    unsplit in the graph (memory allocated in a capture would belong to the graph), and later
+    eager calls on that stream get a workspace of their own."""
+    M, N, K = 16, 4096, 14336
+    assert b.gemm_plan(dtype, M, N, K, K, N, N, 1 << 40, 2 << 40, 3 << 40)["split_k"] > 1
+    A, B, dA, lda, dB, ldb = _operands(dtype, M, N, K, seed=84)
+    fn = b.gemm_i8_i32 if dtype == I8 else b.gemm_bf16_f32
+    assert b.gemm_release_workspace() == b.GEMM_OK
+    s = torch.cuda.Stream()
+    dC, ldc = g.out_buffer(M, N, dtype)
+
+    def gemm():
+        return fn(M, N, K, dA.data_ptr(), lda, dB.data_ptr(), ldb, dC.data_ptr(), ldc, s.cuda_stream)
+
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    print("graph capture without a workspace", flush=True)
+    with torch.cuda.graph(graph, stream=s):
+        rc = gemm()
+    assert rc == b.GEMM_OK
+    first = None
+    for rep in range(4):
+        with torch.cuda.stream(s):
+            dC.fill_(-2 - rep)
+        print(f"graph replay {rep}", flush=True)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = dC.cpu().numpy()[: M * ldc].reshape(M, ldc)[:, :N].copy()
+        if first is None:
+            first = got
+            (g.check_i8 if dtype == I8 else g.check_bf16)(A, B, got)
+        assert np.array_equal(got.view(np.uint32), first.view(np.uint32)), f"replay {rep} differs"
+        assert gemm() == b.GEMM_OK                     # eager, with a workspace of its own
+        s.synchronize()
+        (g.check_i8 if dtype == I8 else g.check_bf16)(A, B, dC.cpu().numpy()[: M * ldc].reshape(M, ldc)[:, :N])
