@@ -30,12 +30,12 @@ def _reset_plan():
 
 def _dev(x, pad, off):
     """x on the GPU with `pad` elements between rows and `off` before the first; what is not
-    the matrix is NaN (bf16) or -128, and the buffer ends with the matrix."""
+    the matrix is NaN (bf16) or -128, 64 elements after the last row too."""
     rows, cols = x.shape
     host = x.view(np.int16) if x.dtype == np.uint16 else x
     fill = np.array(0x7FC1 if x.dtype == np.uint16 else -128).astype(host.dtype)
     ld = cols + pad
-    flat = np.full(off + (rows - 1) * ld + cols, fill, dtype=host.dtype)
+    flat = np.full(off + (rows - 1) * ld + cols + 64, fill, dtype=host.dtype)
     np.lib.stride_tricks.as_strided(flat[off:], (rows, cols), (ld * host.itemsize, host.itemsize))[:] = host
     return torch.from_numpy(flat).to(g.DEV), ld
 

@@ -19,8 +19,8 @@ import gpu_helpers as g
 pytestmark = pytest.mark.gpu
 I8, BF = g.I8, g.BF
 # One or two configurations of every kernel family; GEMV (26 row-major, 27 column-major) for M = 1.
-CONFIGS = [0, 2, 6, 8, 10, 13, 14, 16, 20]
-BT_CONFIGS = [0, 10, 16, 20]
+CONFIGS = [0, 2, 6, 8, 10, 13, 14, 16, 20, 41, 42, 43, 44, 45]
+BT_CONFIGS = [0, 10, 16, 20, 41, 42, 43, 44, 45]
 SHAPES = [(300, 272, 1040), (64, 256, 128), (1, 48, 528)]
 I8_EPILOGUES = [("i8", 0), ("i8", 6), ("i8", 12), ("i8", 17), ("i16", 0), ("i16", 9), ("i16", 14)]
 SENTINEL = {"i8": -77, "i16": -7777, "bf16": 0x7FC1}

@@ -78,7 +78,8 @@ def _gemm(kernels):
 
 def test_every_gemm_kernel_present(kernels):
     names = _gemm(kernels)
-    for fam in ("gemm_lds_kernel", "gemm_ring_kernel", "gemm_tile_kernel", "gemm_vec_kernel",
+    for fam in ("gemm_lds_kernel", "gemm_pingpong_kernel", "gemm_ring_kernel", "gemm_tile_kernel",
+                "gemm_element_kernel", "gemm_vec_kernel",
                 "gemm_stream_kernel", "gemv_kernel", "gemv_bt_kernel"):
         assert any(fam in n for n in names), fam
 
@@ -90,8 +91,10 @@ def test_gemm_kernels_keep_accumulators_in_registers(kernels):
 
 
 def test_8192_plan_kernels_use_no_scratch(kernels):
-    # direct_256x256_w8t, the plan of every 8192^3 case, and its ring counterpart.
-    for pat in (r"gemm_lds_kernelILi[01]ELi256ELi256ELi4ELi2ELi2ELb[01]E",
+    # The ping-pong kernel, the plan of every 8192^3 case, and the 256 x 256 kernels of eight
+    # waves beside it.
+    for pat in (r"gemm_pingpong_kernelILi[01]ELb[01]E",
+                r"gemm_lds_kernelILi[01]ELi256ELi256ELi4ELi2ELi2ELb[01]E",
                 r"gemm_ring_kernelILi[01]ELi256ELi256ELi4ELi2ELi2ELb[01]ELi[45]E"):
         hits = {n: k for n, k in _gemm(kernels).items() if re.search(pat, n)}
         assert len(hits) >= 4, pat
@@ -119,15 +122,19 @@ def _config_kernels(cfg, index, kernels):
     f, bm, bn, wm, wn, st = cfg["family"], cfg["bm"], cfg["bn"], cfg["wm"], cfg["wn"], cfg["stages"]
     geo = rf"ELi{bm}ELi{bn}ELi{wm}ELi{wn}E"
     if f == "FAM_GENERIC":
-        pat = rf"gemm_tile_kernelILi[01]{geo}Lb0E"
+        pat = rf"gemm_tile_kernelILi[01]{geo}Lb[01]E"
     elif f in ("FAM_MACRO", "FAM_SKINNY") and index not in (14, 15):
         pat = rf"gemm_vec_kernelILi[01]{geo}"
     elif index in (14, 15):
         pat = rf"gemm_stream_kernelILi[01]ELi{bm}ELi{st}E"
     elif index == 13:
-        pat = r"gemm_pingpong_kernel"
+        pat = r"gemm_pingpong_kernelILi[01]ELb0E"
+    elif cfg["name"].startswith("quad"):
+        pat = r"gemm_pingpong_kernelILi[01]ELb[01]E"
+    elif f == "FAM_DIRECT" and st > 2:
+        pat = rf"gemm_lds_kernelILi[01]{geo}Li\d+ELb[01]ELi{st}E"
     elif f == "FAM_DIRECT":
-        pat = rf"gemm_lds_kernelILi[01]{geo}Li\d+ELb[01]E"
+        pat = rf"gemm_lds_kernelILi[01]{geo}Li\d+ELb[01]EEEv"
     elif f == "FAM_RING":
         pat = rf"gemm_ring_kernelILi[01]{geo}Li\d+ELb[01]ELi{st}E"
     else:
@@ -140,14 +147,31 @@ def test_config_occupancy_fits_the_cu(kernels):
     must be what the built kernels allow: occupancy x LDS within the CU's 160 KiB, and
     occupancy x waves per SIMD x registers per wave within a SIMD's 512 registers per lane."""
     cfgs = _configs()
-    assert len(cfgs) >= 41
+    assert len(cfgs) >= 46
     for i, c in enumerate(cfgs):
         ks = _config_kernels(c, i, kernels)
-        assert ks, (i, c["name"])
-        waves_per_simd = -(-c["wm"] * c["wn"] // 4) if c["family"] != "FAM_GEMV" else 1
-        for n, k in ks.items():
-            lds = int(k["group_segment_fixed_size"])
-            assert c["occupancy"] * lds <= LDS_LIMIT, (c["name"], n, lds)
-            regs = int(k.get("vgpr_count", 0)) + int(k.get("agpr_count", 0))
-            regs = -(-regs // 8) * 8
-            assert c["occupancy"] * waves_per_simd * regs <= 512, (c["name"], n, regs)
+        layouts = 1 if c["family"] == "FAM_GEMV" else 1 + c["col_major_b"]
+        assert len(ks) == 2 * layouts, (i, c["name"], sorted(ks))
+        _fits(c["name"], c["occupancy"], -(-c["wm"] * c["wn"] // 4) if c["family"] != "FAM_GEMV" else 1, ks)
+
+
+def _fits(name, occupancy, waves_per_simd, ks):
+    for n, k in ks.items():
+        lds = int(k["group_segment_fixed_size"])
+        assert occupancy * lds <= LDS_LIMIT, (name, n, lds)
+        regs = int(k.get("vgpr_count", 0)) + int(k.get("agpr_count", 0))
+        regs = -(-regs // 8) * 8
+        assert occupancy * waves_per_simd * regs <= 512, (name, n, regs)
+
+
+def test_element_kernel_occupancy_fits_the_cu(kernels):
+    """The same for the element-wise kernel, which configurations 0 and 1 run for rows of under
+    16 bytes and strides past 4 MiB, with an occupancy of its own in the model."""
+    src = open(os.path.join(ROOT, "paper_2512_13282_amd", "csrc", "configs.h")).read()
+    own = [int(x) for x in re.findall(r"\{(\d+), [\d.]+, [\d.]+\}", re.search(r"kElementKernels\[2\] = (.*);", src).group(1))]
+    assert len(own) == 2
+    for c, occupancy in zip(_configs(), own):
+        geo = rf"gemm_element_kernelILi[01]ELi{c['bm']}ELi{c['bn']}ELi2ELi2E"
+        ks = {n: k for n, k in _gemm(kernels).items() if re.search(geo, n)}
+        assert len(ks) == 4, (c["name"], sorted(ks))
+        _fits(c["name"], occupancy, 1, ks)
