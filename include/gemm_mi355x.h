@@ -27,10 +27,12 @@
  * keeps no reference after a call returns.  The only memory it allocates is
  * the split-K workspace (partial sums and per-tile arrival counters), one per
  * (device, stream): taken with hipMallocAsync on `stream` at the first split-K
- * call that needs it, grown the same way (the old buffer released with
- * hipFreeAsync on that stream), and kept until the process ends.  Calls on one
+ * call that needs it, grown the same way (to at least twice its size; the buffer
+ * it replaces stays allocated, since a graph captured on the stream may use it),
+ * and kept until the process ends or gemm_release_workspace.  Calls on one
  * stream run in order and share it safely; calls on different streams use
- * different workspaces.  A stream handle that is destroyed and re-created with
+ * different workspaces.  A captured call uses the workspace of the stream it was
+ * captured on: its replays must be ordered with that stream's other calls.  A stream handle that is destroyed and re-created with
  * the same value while work of the old one is still running must not be used.
  *
  * Execution: every GEMM call is asynchronous on `stream` (a hipStream_t passed
@@ -292,7 +294,8 @@ int gemm_clear_plans(void);
 
 /* Frees the split-K workspaces the library holds (every device and stream).
  * Synchronizes each device that holds one first, so it must not be called while
- * another thread is issuing GEMM calls; later split-K calls allocate afresh.
+ * another thread is issuing GEMM calls, and graphs that captured split-K calls
+ * must not be replayed afterwards; later split-K calls allocate afresh.
  * Returns GEMM_OK, or GEMM_ERR_HIP if a synchronization or free failed. */
 int gemm_release_workspace(void);
 

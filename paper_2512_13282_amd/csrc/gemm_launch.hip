@@ -44,9 +44,11 @@ __global__ __launch_bounds__(256) void zero_u32_kernel(uint32_t *__restrict__ p,
 // Split-K workspace, one per (device, stream): the partial planes and the
 // per-tile arrival counters.  Kept for the life of the process and grown on
 // demand, so a split-K call costs no allocation and no extra launch.  Every
-// buffer is allocated, zeroed (counters) and released in stream order on the
-// stream that uses it, so work still queued with an old buffer is unaffected
-// by its replacement.  Launches on one stream run in order and each launch
+// buffer is allocated and zeroed (counters) in stream order on the stream that
+// uses it.  A buffer that growth replaces is kept beside its successor: work
+// still queued and graphs captured on the stream hold its address.  Each is at
+// least twice the one before it, so the replaced ones together stay below the
+// current one's size.  Launches on one stream run in order and each launch
 // leaves every counter it touched at zero, which is what makes the counters
 // reusable; separate streams get separate workspaces.
 namespace {
@@ -55,6 +57,11 @@ struct Workspace {
     size_t partial_bytes = 0;
     uint32_t *counters = nullptr;
     int64_t counter_cap = 0;
+    void *replaced[64] = {};     // doubling from 1 MiB and from 16 KiB, a GPU's memory ends both far earlier
+    int num_replaced = 0;
+    void replace(void *p) {
+        if (p != nullptr) replaced[num_replaced++] = p;
+    }
 };
 std::mutex g_ws_mu;
 std::map<std::pair<int, uintptr_t>, Workspace> g_ws;
@@ -87,22 +94,18 @@ static int acquire_workspace(hipStream_t stream, size_t partial_bytes, int64_t c
         if (capture == hipStreamCaptureStatusActive) return LAUNCH_CAPTURING;
     }
     if (w.partial_bytes < partial_bytes) {
-        if (w.partials != nullptr && hipFreeAsync(w.partials, stream) != hipSuccess) return LAUNCH_HIP_ERROR;
-        w.partials = nullptr;
         const size_t bytes = grow(partial_bytes, w.partial_bytes, size_t(1) << 20);
-        w.partial_bytes = 0;
-        if (hipMallocAsync(&w.partials, bytes, stream) != hipSuccess || w.partials == nullptr) {
+        void *p = nullptr;
+        if (hipMallocAsync(&p, bytes, stream) != hipSuccess || p == nullptr) {
             (void)hipGetLastError();
-            w.partials = nullptr;
             return LAUNCH_NO_MEMORY;
         }
+        w.replace(w.partials);
+        w.partials = p;
         w.partial_bytes = bytes;
     }
     if (w.counter_cap < counter_words) {
-        if (w.counters != nullptr && hipFreeAsync(w.counters, stream) != hipSuccess) return LAUNCH_HIP_ERROR;
-        w.counters = nullptr;
         const int64_t cap = int64_t(grow(size_t(counter_words), size_t(w.counter_cap), 4096));
-        w.counter_cap = 0;
         void *p = nullptr;
         if (hipMallocAsync(&p, size_t(cap) * 4, stream) != hipSuccess || p == nullptr) {
             (void)hipGetLastError();
@@ -116,6 +119,7 @@ static int acquire_workspace(hipStream_t stream, size_t partial_bytes, int64_t c
             (void)hipFreeAsync(p, stream);
             return LAUNCH_HIP_ERROR;
         }
+        w.replace(w.counters);
         w.counters = static_cast<uint32_t *>(p);
         w.counter_cap = cap;
     }
@@ -138,6 +142,8 @@ int release_workspaces() {
         }
         if (w.partials != nullptr && hipFree(w.partials) != hipSuccess) rc = LAUNCH_HIP_ERROR;
         if (w.counters != nullptr && hipFree(w.counters) != hipSuccess) rc = LAUNCH_HIP_ERROR;
+        for (int i = 0; i < w.num_replaced; ++i)
+            if (hipFree(w.replaced[i]) != hipSuccess) rc = LAUNCH_HIP_ERROR;
         w = Workspace{};
     }
     g_ws.clear();

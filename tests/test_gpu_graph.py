@@ -159,3 +159,55 @@ def test_capture_without_a_workspace_allocates_nothing(dtype):
         assert gemm() == b.GEMM_OK                     # eager, with a workspace of its own
         s.synchronize()
         (g.check_i8 if dtype == I8 else g.check_bf16)(A, B, dC.cpu().numpy()[: M * ldc].reshape(M, ldc)[:, :N])
+
+
+@pytest.mark.parametrize("dtype,reduce", [(BF, b.GEMM_REDUCE_SEPARATE), (BF, b.GEMM_REDUCE_LAST_SLICE),
+                                          (I8, b.GEMM_REDUCE_ATOMIC_FLAG)], ids=["sep", "last", "flag"])
+def test_growth_leaves_a_captured_graphs_workspace(dtype, reduce):
+    """A graph keeps the workspace that it captured: a larger eager call on the same stream takes
+    a new one, and another stream's calls (which would be given freed memory) take theirs, while
+    the graph's replays stay bit for bit what they were."""
+    M, N, K = 48, 4112, 4096
+    assert b.gemm_release_workspace() == b.GEMM_OK
+    A, B, dA, lda, dB, ldb = _operands(dtype, M, N, K, seed=86)
+    fn = b.gemm_i8_i32 if dtype == I8 else b.gemm_bf16_f32
+    check = g.check_i8 if dtype == I8 else g.check_bf16
+    s, other = torch.cuda.Stream(), torch.cuda.Stream()
+    dC, ldc = g.out_buffer(M, N, dtype)
+    M2, N2, K2 = 96, 40960, 256                                # 8x the outputs, 20x the tiles
+    A2, B2, dA2, lda2, dB2, ldb2 = _operands(dtype, M2, N2, K2, seed=87)
+    dC2, ldc2 = g.out_buffer(M2, N2, dtype)
+
+    def small(st, c=dC):
+        g.force(dtype, b.GEMM_KERNEL_AUTO, 28, 4, reduce)
+        return fn(M, N, K, dA.data_ptr(), lda, dB.data_ptr(), ldb, c.data_ptr(), ldc, st.cuda_stream)
+
+    def large(st):
+        g.force(dtype, b.GEMM_KERNEL_AUTO, 20, 2, reduce)      # 32 x 64 tiles
+        return fn(M2, N2, K2, dA2.data_ptr(), lda2, dB2.data_ptr(), ldb2, dC2.data_ptr(), ldc2, st.cuda_stream)
+
+    torch.cuda.synchronize()
+    assert small(s) == b.GEMM_OK
+    s.synchronize()
+    eager = dC.cpu().numpy()[: M * ldc].reshape(M, ldc)[:, :N].copy()
+    check(A, B, eager)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        assert small(s) == b.GEMM_OK
+    print(f"graph captured dtype={dtype} reduce={reduce}; the workspace grows", flush=True)
+    assert large(s) == b.GEMM_OK
+    s.synchronize()
+    check(A2, B2, dC2.cpu().numpy()[: M2 * ldc2].reshape(M2, ldc2)[:, :N2])
+    dC3, _ = g.out_buffer(M, N, dtype)
+    for rep in range(3):
+        with torch.cuda.stream(s):
+            dC.fill_(-2 - rep)
+        torch.cuda.synchronize()
+        print(f"graph replay {rep} beside another stream", flush=True)
+        graph.replay()
+        for _ in range(3):
+            assert small(other, dC3) == b.GEMM_OK
+        torch.cuda.synchronize()
+        for c in (dC, dC3):
+            got = c.cpu().numpy()[: M * ldc].reshape(M, ldc)[:, :N]
+            assert np.array_equal(got.view(np.uint32), eager.view(np.uint32)), f"replay {rep} differs"
