@@ -37,10 +37,10 @@
  *
  * Execution: every GEMM call is asynchronous on `stream` (a hipStream_t passed
  * as void*; NULL = the null stream) and never synchronizes the device.  A call
- * may be captured into a HIP graph.  The workspace does not grow in a capture: a
- * call whose split-K plan needs more than `stream` holds then runs the best plan
- * without a split (a forced or loaded plan is left as it is), so run it once on
- * the stream beforehand if the captured call is to split K too.
+ * may be captured into a HIP graph.  A captured split-K call whose stream holds no
+ * workspace of its size takes one with hipMalloc (ordinary memory, not the graph's)
+ * and sums its slices in a kernel of their own: the same result, and a few
+ * microseconds more at each replay than if the call had run on the stream before.
  *
  * Errors: every entry point returns an int status (gemm_status_t) and never
  * throws or aborts.  Argument checks run on the host BEFORE any HIP call:

@@ -250,8 +250,7 @@ int run(int32_t dtype, int32_t trans_b, int64_t M, int64_t N, int64_t K, const v
     if (rc != GEMM_OK) return rc;
     if (M == 0 || N == 0) return GEMM_OK;
     Plan pl;
-    int32_t source = GEMM_PLAN_FROM_MODEL;
-    rc = plan_for(p, &pl, &source, static_scratch);
+    rc = plan_for(p, &pl, nullptr, static_scratch);
     if (rc != GEMM_OK) return rc;
 
     gemm::KernelArgs a{};
@@ -268,24 +267,18 @@ int run(int32_t dtype, int32_t trans_b, int64_t M, int64_t N, int64_t K, const v
     a.b_trans = trans_b;
     a.epilogue = epilogue;
     a.shift = shift;
-    a.callers_plan = source == GEMM_PLAN_FROM_FORCED || source == GEMM_PLAN_FROM_FILE;
-    int lr;
-    do {
-        a.k_chunk = pl.k_chunk;
-        a.split_k = pl.split_k;
-        a.tiles_m = int32_t(pl.tiles_m);
-        a.tiles_n = int32_t(pl.tiles_n);
-        a.reduce_in_kernel = pl.reduce_in_kernel;
-        // The atomic reductions add int32 partials into C: narrowed outputs take the separate one.
-        if ((a.reduce_in_kernel == gemm::REDUCE_ATOMIC || a.reduce_in_kernel == gemm::REDUCE_ATOMIC_FLAG) &&
-            epilogue != gemm::EPI_NONE)
-            a.reduce_in_kernel = gemm::REDUCE_SEPARATE;
-        if (pl.grid > 0x7fffffff || pl.tiles_m > 0x7fffffff || pl.tiles_n > 0x7fffffff)
-            return GEMM_ERR_UNSUPPORTED;
-        lr = gemm::launch_gemm(a, pl.config, pl.grid, stream, static_scratch);
-        // In a capture that would have to allocate the workspace: the best unsplit plan.
-        if (lr == gemm::LAUNCH_CAPTURING && !gemm::select_plan(p, &pl, -1, -1, 1)) return GEMM_ERR_UNSUPPORTED;
-    } while (lr == gemm::LAUNCH_CAPTURING);
+    a.k_chunk = pl.k_chunk;
+    a.split_k = pl.split_k;
+    a.tiles_m = int32_t(pl.tiles_m);
+    a.tiles_n = int32_t(pl.tiles_n);
+    a.reduce_in_kernel = pl.reduce_in_kernel;
+    // The atomic reductions add int32 partials into C: narrowed outputs take the separate one.
+    if ((a.reduce_in_kernel == gemm::REDUCE_ATOMIC || a.reduce_in_kernel == gemm::REDUCE_ATOMIC_FLAG) &&
+        epilogue != gemm::EPI_NONE)
+        a.reduce_in_kernel = gemm::REDUCE_SEPARATE;
+    if (pl.grid > 0x7fffffff || pl.tiles_m > 0x7fffffff || pl.tiles_n > 0x7fffffff)
+        return GEMM_ERR_UNSUPPORTED;
+    const int lr = gemm::launch_gemm(a, pl.config, pl.grid, stream, static_scratch);
     if (lr == gemm::LAUNCH_NO_MEMORY) return GEMM_ERR_NO_MEMORY;
     if (lr == gemm::LAUNCH_SCRATCH_LIMIT) return GEMM_ERR_SCRATCH_LIMIT;
     if (lr != gemm::LAUNCH_OK) return GEMM_ERR_HIP;

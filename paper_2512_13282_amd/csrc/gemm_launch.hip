@@ -81,25 +81,50 @@ static bool fail_workspace_for_test() {
     return e != nullptr && e[0] == '1';
 }
 
-static int acquire_workspace(hipStream_t stream, size_t partial_bytes, int64_t counter_words, bool grow_in_capture,
-                             void **partials, uint32_t **counters) {
+// hipMalloc on a thread that may be capturing `stream`: ordinary memory of the process, where a
+// stream-ordered allocation would become a node of the graph.
+static void *malloc_in_capture(size_t bytes) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    void *p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return p;
+}
+
+// Partials and counters for a call on `stream`, grown where they are too small.  In a capture
+// the counters do not grow (what zeroes them would run at each replay, not now), and the call
+// gets LAUNCH_NO_COUNTERS, before anything is queued.
+static int acquire_workspace(hipStream_t stream, size_t partial_bytes, int64_t counter_words, void **partials,
+                             uint32_t **counters) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return LAUNCH_HIP_ERROR;
     std::lock_guard<std::mutex> lk(g_ws_mu);
     Workspace &w = g_ws[{dev, reinterpret_cast<uintptr_t>(stream)}];
+    bool capturing = false;
     if (w.partial_bytes < partial_bytes || w.counter_cap < counter_words) {
         if (fail_workspace_for_test()) return LAUNCH_NO_MEMORY;
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (!grow_in_capture && hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
-        if (capture == hipStreamCaptureStatusActive) return LAUNCH_CAPTURING;
+        if (hipStreamIsCapturing(stream, &capture) == hipSuccess) capturing = capture == hipStreamCaptureStatusActive;
+        else (void)hipGetLastError();
+        if (capturing && w.counter_cap < counter_words) return LAUNCH_NO_COUNTERS;
     }
     if (w.partial_bytes < partial_bytes) {
         const size_t bytes = grow(partial_bytes, w.partial_bytes, size_t(1) << 20);
         void *p = nullptr;
-        if (hipMallocAsync(&p, bytes, stream) != hipSuccess || p == nullptr) {
+        if (capturing) {
+            p = malloc_in_capture(bytes);
+        } else if (hipMallocAsync(&p, bytes, stream) != hipSuccess) {
             (void)hipGetLastError();
-            return LAUNCH_NO_MEMORY;
+            p = nullptr;
         }
+        if (p == nullptr) return LAUNCH_NO_MEMORY;
         w.replace(w.partials);
         w.partials = p;
         w.partial_bytes = bytes;
@@ -197,14 +222,7 @@ int launch_gemm(const KernelArgs &a, int32_t cfg, int64_t grid, void *stream_ptr
     KernelArgs args = a;
     args.workspace = nullptr;
     args.counters = nullptr;
-    if (args.split_k > 1 && args.reduce_in_kernel == REDUCE_ATOMIC) {
-        if (args.dtype != DT_I8 || args.epilogue != EPI_NONE) return LAUNCH_HIP_ERROR;
-        int64_t blocks = (args.M * args.N + 255) / 256;
-        if (blocks > 2048) blocks = 2048;
-        hipLaunchKernelGGL(zero_c_kernel, dim3(unsigned(blocks)), dim3(256), 0, stream, static_cast<uint32_t *>(args.C),
-                           args.M, args.N, args.ldc);
-        if (hipGetLastError() != hipSuccess) return LAUNCH_HIP_ERROR;
-    } else if (args.split_k > 1) {
+    if (args.split_k > 1 && args.reduce_in_kernel != REDUCE_ATOMIC) {
         const bool flag = args.reduce_in_kernel == REDUCE_ATOMIC_FLAG;
         if (flag && (args.dtype != DT_I8 || args.epilogue != EPI_NONE ||
                      (kConfigs[cfg].family != FAM_RING && kConfigs[cfg].family != FAM_GEMV)))
@@ -230,10 +248,23 @@ int launch_gemm(const KernelArgs &a, int32_t cfg, int64_t grid, void *stream_ptr
                 if (hipGetLastError() != hipSuccess) return LAUNCH_HIP_ERROR;
             }
         } else {
-            const int rc = acquire_workspace(stream, bytes, counter_words, args.callers_plan != 0, &args.workspace,
-                                             &args.counters);
+            int rc = acquire_workspace(stream, bytes, counter_words, &args.workspace, &args.counters);
+            if (rc == LAUNCH_NO_COUNTERS) {
+                // The reductions with one more launch and no counters: the same slices summed in
+                // the same order, or int32 adds in any, so the same bits.
+                args.reduce_in_kernel = flag ? REDUCE_ATOMIC : REDUCE_SEPARATE;
+                rc = flag ? LAUNCH_OK : acquire_workspace(stream, bytes, 0, &args.workspace, &args.counters);
+            }
             if (rc != LAUNCH_OK) return rc;
         }
+    }
+    if (args.split_k > 1 && args.reduce_in_kernel == REDUCE_ATOMIC) {
+        if (args.dtype != DT_I8 || args.epilogue != EPI_NONE) return LAUNCH_HIP_ERROR;
+        int64_t blocks = (args.M * args.N + 255) / 256;
+        if (blocks > 2048) blocks = 2048;
+        hipLaunchKernelGGL(zero_c_kernel, dim3(unsigned(blocks)), dim3(256), 0, stream, static_cast<uint32_t *>(args.C),
+                           args.M, args.N, args.ldc);
+        if (hipGetLastError() != hipSuccess) return LAUNCH_HIP_ERROR;
     }
     hipError_t e = args.dtype == DT_I8 ? launch_config<DT_I8>(cfg, args, grid, stream)
                                        : launch_config<DT_BF16>(cfg, args, grid, stream);

@@ -8,7 +8,6 @@ namespace gemm {
 
 struct KernelArgs {
     int32_t dtype;                 // DT_I8 or DT_BF16
-    int32_t callers_plan;          // 1: forced or from a plan file (host only, see launch_gemm)
     const void *A;
     const void *B;
     void *C;
@@ -50,7 +49,7 @@ enum { REDUCE_SEPARATE = 0, REDUCE_LAST_SLICE = 1, REDUCE_ATOMIC = 2, REDUCE_ATO
 // atomics behind each other (a GEMV with 32 slices per tile ran 1.9x slower).
 constexpr int kFlagCounterStride = 32;
 
-enum { LAUNCH_OK = 0, LAUNCH_HIP_ERROR = 1, LAUNCH_NO_MEMORY = 2, LAUNCH_SCRATCH_LIMIT = 3, LAUNCH_CAPTURING = 4 };
+enum { LAUNCH_OK = 0, LAUNCH_HIP_ERROR = 1, LAUNCH_NO_MEMORY = 2, LAUNCH_SCRATCH_LIMIT = 3, LAUNCH_NO_COUNTERS = 4 };
 
 // The fixed split-K scratch of the entry point that allocates nothing: per device,
 // kScratchCounterBytes of per-tile arrival counters followed by the partial planes.
@@ -60,10 +59,9 @@ constexpr int64_t kScratchCounterBytes = int64_t(64) << 10;
 // Queues the plan's kernels on `stream` (a hipStream_t).  Never synchronizes.  With
 // static_scratch a split-K plan takes its partials and counters from the library's
 // fixed per-device scratch instead of the per-stream workspace (no allocation), or
-// returns LAUNCH_SCRATCH_LIMIT, before queueing anything, when they do not fit.  Returns
-// LAUNCH_CAPTURING, before queueing anything, where the workspace would have to grow while
-// `stream` is being captured and the plan is the library's own (callers_plan == 0): memory
-// allocated in a capture belongs to the graph, and the workspace outlives it.
+// returns LAUNCH_SCRATCH_LIMIT, before queueing anything, when they do not fit.  While
+// `stream` is being captured and its workspace holds too few counters, the reductions that
+// need none take the place of those that do.
 int launch_gemm(const KernelArgs &a, int32_t config, int64_t grid, void *stream, bool static_scratch = false);
 
 // Frees every cached split-K workspace (all devices and streams) after

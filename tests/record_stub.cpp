@@ -7,14 +7,13 @@
 #include "../paper_2512_13282_amd/csrc/launch.h"
 
 static int64_t g_last[8];
-static int g_capturing;     // 1: as on a stream in a capture, whose workspace may not grow
 
 namespace gemm {
 int launch_gemm(const KernelArgs &a, int32_t config, int64_t grid, void *, bool static_scratch) {
     const int64_t v[8] = {config, a.split_k, a.k_chunk, a.reduce_in_kernel, grid, a.epilogue, static_scratch,
                           int64_t(a.tiles_m) * a.tiles_n};
     for (int i = 0; i < 8; ++i) g_last[i] = v[i];
-    return g_capturing && a.split_k > 1 && a.callers_plan == 0 ? LAUNCH_CAPTURING : LAUNCH_OK;
+    return LAUNCH_OK;
 }
 int release_workspaces() { return LAUNCH_OK; }
 }  // namespace gemm
@@ -22,7 +21,6 @@ int release_workspaces() { return LAUNCH_OK; }
 extern "C" void recorded_launch(int64_t *out) {
     for (int i = 0; i < 8; ++i) out[i] = g_last[i];
 }
-extern "C" void record_as_capturing(int on) { g_capturing = on; }
 extern "C" int gemm_probe_mfma(int, int, int32_t, int64_t *, unsigned *, gemm_probe_info *, void *) {
     return GEMM_ERR_HIP;
 }

@@ -122,43 +122,53 @@ def test_graph_replays_noalloc():
         assert np.array_equal(got.view(np.uint32), eager.view(np.uint32)), f"replay {rep} differs"
 
 
-@pytest.mark.parametrize("dtype", [I8, BF], ids=["i8", "bf16"])
-def test_capture_without_a_workspace_allocates_nothing(dtype):
-    """A call whose own plan splits K, captured on a stream that holds no workspace yet: it runs
-    unsplit in the graph (memory allocated in a capture would belong to the graph), and later
-    eager calls on that stream get a workspace of their own."""
+# the library's own plan (reduce None), and each reduction that takes partials or counters
+@pytest.mark.parametrize("dtype,reduce", [(I8, None), (BF, None), (BF, b.GEMM_REDUCE_SEPARATE),
+                                          (BF, b.GEMM_REDUCE_LAST_SLICE), (I8, b.GEMM_REDUCE_LAST_SLICE),
+                                          (I8, b.GEMM_REDUCE_ATOMIC_FLAG)],
+                         ids=["i8-own", "bf16-own", "bf16-sep", "bf16-last", "i8-last", "i8-flag"])
+def test_capture_on_a_stream_without_a_workspace(dtype, reduce):
+    """A split-K call captured on a stream that holds no workspace yet splits K as the eager call
+    does, to the same bits, on memory that is not the graph's: the graph's replays and eager calls
+    on its stream, which use that memory too, leave each other's results alone."""
     M, N, K = 16, 4096, 14336
-    assert b.gemm_plan(dtype, M, N, K, K, N, N, 1 << 40, 2 << 40, 3 << 40)["split_k"] > 1
+    if reduce is not None:
+        g.force(dtype, b.GEMM_KERNEL_AUTO, 28, 4, reduce)
+    p = b.gemm_plan(dtype, M, N, K, K, N, N, 1 << 40, 2 << 40, 3 << 40)
+    assert p["split_k"] > 1 and reduce in (None, p["reduce_in_kernel"])
     A, B, dA, lda, dB, ldb = _operands(dtype, M, N, K, seed=84)
     fn = b.gemm_i8_i32 if dtype == I8 else b.gemm_bf16_f32
     assert b.gemm_release_workspace() == b.GEMM_OK
-    s = torch.cuda.Stream()
+    s, eager_stream = torch.cuda.Stream(), torch.cuda.Stream()
     dC, ldc = g.out_buffer(M, N, dtype)
 
-    def gemm():
-        return fn(M, N, K, dA.data_ptr(), lda, dB.data_ptr(), ldb, dC.data_ptr(), ldc, s.cuda_stream)
+    def gemm(st):
+        return fn(M, N, K, dA.data_ptr(), lda, dB.data_ptr(), ldb, dC.data_ptr(), ldc, st.cuda_stream)
+
+    def result():
+        torch.cuda.synchronize()
+        return dC.cpu().numpy()[: M * ldc].reshape(M, ldc)[:, :N].copy()
 
     torch.cuda.synchronize()
+    assert gemm(eager_stream) == b.GEMM_OK
+    eager = result()
+    (g.check_i8 if dtype == I8 else g.check_bf16)(A, B, eager)
     graph = torch.cuda.CUDAGraph()
-    print("graph capture without a workspace", flush=True)
+    print(f"graph capture without a workspace dtype={dtype} reduce={reduce}", flush=True)
     with torch.cuda.graph(graph, stream=s):
-        rc = gemm()
+        rc = gemm(s)
     assert rc == b.GEMM_OK
-    first = None
     for rep in range(4):
-        with torch.cuda.stream(s):
-            dC.fill_(-2 - rep)
-        print(f"graph replay {rep}", flush=True)
-        graph.replay()
-        torch.cuda.synchronize()
-        got = dC.cpu().numpy()[: M * ldc].reshape(M, ldc)[:, :N].copy()
-        if first is None:
-            first = got
-            (g.check_i8 if dtype == I8 else g.check_bf16)(A, B, got)
-        assert np.array_equal(got.view(np.uint32), first.view(np.uint32)), f"replay {rep} differs"
-        assert gemm() == b.GEMM_OK                     # eager, with a workspace of its own
-        s.synchronize()
-        (g.check_i8 if dtype == I8 else g.check_bf16)(A, B, dC.cpu().numpy()[: M * ldc].reshape(M, ldc)[:, :N])
+        for what in ("replay", "eager"):
+            with torch.cuda.stream(s):
+                dC.fill_(-2 - rep)
+            torch.cuda.synchronize()
+            print(f"{what} {rep}", flush=True)
+            if what == "replay":
+                graph.replay()
+            else:
+                assert gemm(s) == b.GEMM_OK
+            assert np.array_equal(result().view(np.uint32), eager.view(np.uint32)), f"{what} {rep} differs"
 
 
 @pytest.mark.parametrize("dtype,reduce", [(BF, b.GEMM_REDUCE_SEPARATE), (BF, b.GEMM_REDUCE_LAST_SLICE),
