@@ -175,9 +175,12 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     // its slice of A, at a rate one workgroup's loads in flight bound: too few workgroups
     // cannot reach the HBM rate (measured: 112 unsplit workgroups of 32 x 128 at M = 16
     // take 1.4x the time of 224 split ones).
+    // The row-major GEMV walks its rows one after another whatever their width: columns past N
+    // save it nothing (1 x 64 x 11264 int8 in eight slices 40 us, a 32-row ring tile 7.2).
     if (pl.tiles_m == 1 && p.K > 0) {
+        const int64_t cols = c.family == FAM_GEMV ? c.bn : std::min<int64_t>(c.bn, p.N);
         const double wg_bytes = double(std::min<int64_t>(pl.k_chunk, p.K)) *
-                                (double(std::min<int64_t>(c.bm, p.M)) + double(std::min<int64_t>(c.bn, p.N)) * b_line) * e;
+                                (double(std::min<int64_t>(c.bm, p.M)) + double(cols) * b_line) * e;
         pl.t_mem_us = std::max(pl.t_mem_us, double(rounds) * wg_bytes / chip.wg_cold_bytes_per_s * 1e6);
     }
 
@@ -270,8 +273,11 @@ bool select_plan(const Problem &p, Plan *out, int32_t forced_family, int32_t for
             (p.K * elem_bytes(p.dtype) > 2048 || kConfigs[cfg].bm > 64) && vector_loads_ok(p))
             continue;
         // The three-stage 64 x 64 kernel is for tiles more than half full: at M = 6 (bf16
-        // 6 x 12288 x 6592) it took 43 us against 33 of a 32-row tile, at M = 50 (50 x 1600 x
-        // 10944) 12.8 against 15.6.
+        // 6 x 12288 x 6592, B row-major) it took 43 us against 33 of a 32-row tile, at M = 50
+        // (50 x 1600 x 10944) 12.8 against 15.6.  A column-major B moves the line only where it
+        // was measured: measured plans take the kernel from M = 8 on there, and the M = 2 to 31
+        // that borrow them run 0.94 of the time of the 32-row ring tiles (130 calls); but where
+        // the model has to price it, 150 calls of M = 2 to 32 with other N and K run 1.05 times.
         if (forced_family < 0 && forced_config < 0 && kConfigs[cfg].family == FAM_DIRECT && kConfigs[cfg].bm == 64 &&
             p.M <= 32)
             continue;

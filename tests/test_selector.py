@@ -387,3 +387,14 @@ def test_small_int8_products_run_whole():
         assert plan(I8, M, N, K)["split_k"] == 1, (M, N, K)
     assert plan_bt(I8, 1, 1984, 2368)["split_k"] == 1
     assert plan_bt(I8, 1, 2112, 9856)["split_k"] == 2      # 7.8 us, 10.0 whole
+
+
+@pytest.mark.parametrize("dtype", [I8, BF])
+def test_one_row_with_few_columns_is_no_gemv(dtype):
+    """The row-major GEMV walks K at one rate for any width up to its 1024 columns: with a few
+    dozen columns the tile kernels run it in half the time or less."""
+    for N in (16, 48, 64, 128, 256, 400):
+        for K in (208, 1120, 2368, 5536, 11264):
+            assert plan(dtype, 1, N, K)["kernel"] != b.GEMM_KERNEL_GEMV, (N, K)
+    if dtype == I8:
+        assert plan(dtype, 1, 14336, 8192)["kernel"] == b.GEMM_KERNEL_GEMV
