@@ -219,9 +219,12 @@ int gemm_bf16_f32_bt(int64_t M, int64_t N, int64_t K,
  *       bf16, ties to even (raw bf16 bit patterns in C).
  *
  * C is int8_t / int16_t / uint16_t with row stride ldc in ELEMENTS of that type
- * and must be aligned to its element size.  Plans, ownership, workspace,
- * execution and errors are those of the int32 / fp32 calls (the plan does not
- * depend on the output type); a shift outside [0, 31] is GEMM_ERR_INVALID_VALUE.
+ * and must be aligned to its element size.  Ownership, workspace, execution and
+ * errors are those of the int32 / fp32 calls, and so are plans, but that the model
+ * prices an int8 call by its own output: a narrower C is less to write, and K slices
+ * cannot be summed by adding into it (in a measured, loaded or forced plan that says
+ * so a kernel of its own sums them).  gemm_plan describes the int32 and fp32 calls
+ * and gemm_bf16_bf16.  A shift outside [0, 31] is GEMM_ERR_INVALID_VALUE.
  * The *_bt forms take B stored column-major (Bt, N x K) as above. */
 int gemm_i8_i8(int64_t M, int64_t N, int64_t K,
                const int8_t *A, int64_t lda,
@@ -248,8 +251,9 @@ int gemm_bf16_bf16_bt(int64_t M, int64_t N, int64_t K,
                       const uint16_t *Bt, int64_t ldbt,
                       uint16_t *C, int64_t ldc, void *stream);
 
-/* Pure host: the plan a GEMM call with these arguments would use (alignment
- * is taken from the three addresses, which are never dereferenced).
+/* Pure host: the plan that gemm_i8_i32 or gemm_bf16_f32 (and gemm_bf16_bf16) would
+ * use with these arguments (alignment is taken from the three addresses, which are
+ * never dereferenced).
  * Returns GEMM_OK, GEMM_ERR_INVALID_VALUE or GEMM_ERR_UNSUPPORTED. */
 int gemm_plan(int dtype, int64_t M, int64_t N, int64_t K,
               int64_t lda, int64_t ldb, int64_t ldc,

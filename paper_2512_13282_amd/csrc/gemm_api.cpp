@@ -38,11 +38,11 @@ struct Key {
     int32_t dtype;
     int64_t M, N, K;
     int32_t align;     // alignment_class
-    int32_t trans_b;
+    int32_t trans_b, c_bytes;
     int32_t fixed_scratch;
     bool operator==(const Key &o) const {
         return dtype == o.dtype && M == o.M && N == o.N && K == o.K && align == o.align && trans_b == o.trans_b &&
-               fixed_scratch == o.fixed_scratch;
+               c_bytes == o.c_bytes && fixed_scratch == o.fixed_scratch;
     }
 };
 // 64-bit FNV-1a over the key's fields (its published offset basis and prime).
@@ -51,7 +51,8 @@ struct KeyHash {
         uint64_t h = 1469598103934665603ULL;
         auto mix = [&](uint64_t v) { h = (h ^ v) * 1099511628211ULL; };
         mix(uint64_t(k.dtype)); mix(uint64_t(k.M)); mix(uint64_t(k.N)); mix(uint64_t(k.K));
-        mix(uint64_t(k.align)); mix(uint64_t(k.trans_b)); mix(uint64_t(k.fixed_scratch));
+        mix(uint64_t(k.align)); mix(uint64_t(k.trans_b)); mix(uint64_t(k.c_bytes));
+        mix(uint64_t(k.fixed_scratch));
         return size_t(h);
     }
 };
@@ -72,7 +73,7 @@ struct Shape {
     }
 };
 struct ShapeHash {
-    size_t operator()(const Shape &s) const { return KeyHash()(Key{s.dtype, s.M, s.N, s.K, 0, s.trans_b, 0}); }
+    size_t operator()(const Shape &s) const { return KeyHash()(Key{s.dtype, s.M, s.N, s.K, 0, s.trans_b, 4, 0}); }
 };
 struct LoadedPlan {
     int32_t config, split, reduce;
@@ -196,7 +197,7 @@ int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr, bool fixed_
     }
     const bool forced = ov.family >= 0 || ov.config >= 0 || ov.split > 0 || ov.reduce >= 0;
     if (!forced) {
-        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b, fixed_scratch};
+        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b, p.c_bytes, fixed_scratch};
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_cache.find(key);
         if (it != g_cache.end()) {
@@ -230,7 +231,7 @@ int plan_for(const Problem &p, Plan *out, int32_t *source = nullptr, bool fixed_
                       : gemm::neighbour_plan(p, &cfg, &split, &reduce) ? GEMM_PLAN_FROM_NEIGHBOUR
                       : GEMM_PLAN_FROM_MODEL;
     if (!forced) {
-        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b, fixed_scratch};
+        const Key key{p.dtype, p.M, p.N, p.K, gemm::alignment_class(p), p.trans_b, p.c_bytes, fixed_scratch};
         std::lock_guard<std::mutex> lk(g_mu);
         if (g_cache.size() > 4096) g_cache.clear();
         g_cache.emplace(key, CachedPlan{pl, src});
@@ -245,6 +246,8 @@ int run(int32_t dtype, int32_t trans_b, int64_t M, int64_t N, int64_t K, const v
         int32_t epilogue = gemm::EPI_NONE, int32_t shift = 0, bool static_scratch = false) {
     Problem p{dtype, M, N, K, lda, ldb, ldc, uintptr_t(A), uintptr_t(B), uintptr_t(C), trans_b};
     const int64_t c_esize = epilogue == gemm::EPI_I8 ? 1 : (epilogue == gemm::EPI_NONE ? 4 : 2);
+    // gemm_bf16_bf16 rounds the sums of gemm_bf16_f32: its plan is that call's.
+    if (dtype == gemm::DT_I8) p.c_bytes = int32_t(c_esize);
     if (shift < 0 || shift > 31) return GEMM_ERR_INVALID_VALUE;
     int rc = validate(p, A, B, C, c_esize);
     if (rc != GEMM_OK) return rc;
@@ -272,10 +275,6 @@ int run(int32_t dtype, int32_t trans_b, int64_t M, int64_t N, int64_t K, const v
     a.tiles_m = int32_t(pl.tiles_m);
     a.tiles_n = int32_t(pl.tiles_n);
     a.reduce_in_kernel = pl.reduce_in_kernel;
-    // The atomic reductions add int32 partials into C: narrowed outputs take the separate one.
-    if ((a.reduce_in_kernel == gemm::REDUCE_ATOMIC || a.reduce_in_kernel == gemm::REDUCE_ATOMIC_FLAG) &&
-        epilogue != gemm::EPI_NONE)
-        a.reduce_in_kernel = gemm::REDUCE_SEPARATE;
     if (pl.grid > 0x7fffffff || pl.tiles_m > 0x7fffffff || pl.tiles_n > 0x7fffffff)
         return GEMM_ERR_UNSUPPORTED;
     const int lr = gemm::launch_gemm(a, pl.config, pl.grid, stream, static_scratch);

@@ -111,7 +111,11 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
                      : p.dtype == DT_I8 ? ((c.family == FAM_RING || c.family == FAM_GEMV) ? REDUCE_ATOMIC_FLAG
                                                                                        : REDUCE_ATOMIC)
                      : (in_kernel_us <= chip.last_slice_below_us ? REDUCE_LAST_SLICE : REDUCE_SEPARATE);
-        if ((mode == REDUCE_ATOMIC || mode == REDUCE_ATOMIC_FLAG) && p.dtype != DT_I8) mode = REDUCE_SEPARATE;
+        // Adds into C need an int32 C.  Narrowed int8 calls are priced without them, and by their own
+        // width of C: with the int32 call's plans 57 of 340 ran more than 5 % slower (12 x 1024 x 320
+        // 4.4 us whole, 7.8 in three slices summed apart).
+        if ((mode == REDUCE_ATOMIC || mode == REDUCE_ATOMIC_FLAG) && (p.dtype != DT_I8 || p.c_bytes != 4))
+            mode = REDUCE_SEPARATE;
         if (mode == REDUCE_ATOMIC_FLAG && c.family != FAM_RING && c.family != FAM_GEMV) mode = REDUCE_ATOMIC;
         pl.reduce_in_kernel = mode;
         // Atomic with slice 0's zeros: what the other slices wait for beyond their own work.  At
@@ -162,7 +166,7 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     // 128-column ones).
     const double b_line = (!p.trans_b && c.bn * e < 128) ? 128.0 / double(c.bn * e) : 1.0;
     const double a_bytes = double(p.M) * p.K * e, b_bytes = double(p.K) * p.N * e * b_line;
-    const double c_bytes = double(p.M) * p.N * 4;
+    const double c_bytes = double(p.M) * p.N * p.c_bytes;
     const double a_reads = a_bytes * double(pl.tiles_n);
     const double b_reads = b_bytes * double(pl.tiles_m);
     const double ws = partial_planes ? 2.0 * double(pl.workspace_bytes)

@@ -13,6 +13,7 @@ struct Problem {
     int64_t lda, ldb, ldc;
     uintptr_t a_addr, b_addr, c_addr;
     int32_t trans_b = 0;   // 1: B stored column-major (N x K, row stride ldb)
+    int32_t c_bytes = 4;   // of an output: 1 or 2 for int8 narrowed, whose slices cannot be added into C
 };
 
 struct Plan {
@@ -63,7 +64,7 @@ int32_t stage_k_elems(int32_t dtype);    // K elements per 128-byte LDS stage
 bool vector_loads_ok(const Problem &p);
 
 // What a call's addresses and strides allow, as bits: everything a plan depends on beside
-// dtype, sizes and B's layout (plans are cached by both).
+// dtype, sizes, B's layout and an int8 call's output width (plans are cached by all of them).
 enum : int32_t { ALIGN_VECTOR = 1, ALIGN_WIDE = 2 };
 int32_t alignment_class(const Problem &p);
 

@@ -59,22 +59,55 @@ def _shapes(n, seed):
         yield M, N, K, rng.randint(0, 1)
 
 
-def test_plan_does_not_depend_on_the_output_type(rec):
-    """The narrowed calls run the tile, split and K slices of the int32 / fp32 call, which is
-    what gemm_plan reports: the fp32 sums that gemm_bf16_bf16 rounds are gemm_bf16_f32's."""
+SAME = ("config", "split_k", "k_chunk", "grid")
+ATOMIC = (b.GEMM_REDUCE_ATOMIC, b.GEMM_REDUCE_ATOMIC_FLAG)
+
+
+def test_bf16_plans_do_not_depend_on_the_output_type(rec):
+    """gemm_bf16_bf16 runs the tile, K slices and reduction of gemm_bf16_f32, which are what
+    gemm_plan reports: the fp32 sums that it rounds are that call's."""
     known = [(192, 1984, 2624, 1), (3424, 128, 7680, 0), (589, 771, 1647, 1), (128, 704, 6272, 1)]
-    same = ("config", "split_k", "k_chunk", "grid")
     for M, N, K, bt in known + list(_shapes(300, 1)):
-        for dtype, wide, narrow in ((BF, "gemm_bf16_f32", ["gemm_bf16_bf16"]),
-                                    (I8, "gemm_i8_i32", ["gemm_i8_i8", "gemm_i8_i16"])):
-            p = rec.plan(dtype, M, N, K, bt)
-            rc, w = rec.call(wide, M, N, K, bt)
-            assert rc == b.GEMM_OK and [w[k] for k in same] == [p.config, p.split_k, p.k_chunk, p.grid]
-            for name in narrow:
-                rc, x = rec.call(name, M, N, K, bt)
-                assert rc == b.GEMM_OK and [x[k] for k in same] == [w[k] for k in same], (name, M, N, K, bt, x, w)
-                if x["split_k"] > 1:     # int32 sums added into C need an int32 C
-                    assert x["reduce"] == (w["reduce"] if w["reduce"] <= b.GEMM_REDUCE_LAST_SLICE else 0)
+        p = rec.plan(BF, M, N, K, bt)
+        for name in ("gemm_bf16_f32", "gemm_bf16_bf16"):
+            rc, x = rec.call(name, M, N, K, bt)
+            assert rc == b.GEMM_OK and [x[k] for k in SAME] == [p.config, p.split_k, p.k_chunk, p.grid], (name, M, N, K)
+            assert x["split_k"] == 1 or x["reduce"] == p.reduce_in_kernel
+
+
+def test_narrowed_int8_plans(rec):
+    """gemm_i8_i32 runs what gemm_plan reports.  The narrowed calls run measured and forced plans
+    too, and plans of their own elsewhere; none adds K slices into C."""
+    tuned = [(16, 4096, 14336, 0), (2048, 4096, 11008, 1), (48, 14336, 4096, 1), (64, 4096, 14336, 1)]
+    for M, N, K, bt in tuned + list(_shapes(300, 4)):
+        p = rec.plan(I8, M, N, K, bt)
+        rc, w = rec.call("gemm_i8_i32", M, N, K, bt)
+        assert rc == b.GEMM_OK and [w[k] for k in SAME] == [p.config, p.split_k, p.k_chunk, p.grid]
+        for name in ("gemm_i8_i8", "gemm_i8_i16"):
+            rc, x = rec.call(name, M, N, K, bt)
+            assert rc == b.GEMM_OK and (x["split_k"] == 1 or x["reduce"] not in ATOMIC), (name, M, N, K, bt, x)
+            if (M, N, K, bt) in tuned:
+                assert p.source != b.GEMM_PLAN_FROM_MODEL and [x[k] for k in SAME] == [w[k] for k in SAME]
+    for reduce in ATOMIC:
+        rec.lib.gemm_force_plan(I8, b.GEMM_KERNEL_AUTO, 28, 4)
+        rec.lib.gemm_force_reduce(I8, reduce)
+        try:
+            assert rec.call("gemm_i8_i32", 16, 4096, 14336, 0)[1]["reduce"] == reduce
+            rc, x = rec.call("gemm_i8_i8", 16, 4096, 14336, 0)
+            assert rc == b.GEMM_OK and (x["config"], x["split_k"], x["reduce"]) == (28, 4, b.GEMM_REDUCE_SEPARATE)
+        finally:
+            rec.lib.gemm_force_reduce(I8, -1)
+            rec.lib.gemm_force_plan(I8, b.GEMM_KERNEL_AUTO, -1, 0)
+
+
+@pytest.mark.parametrize("M,N,K,bt", [(12, 1024, 320, 1), (16, 64, 384, 1), (3, 64, 512, 0), (50, 3712, 512, 1),
+                                      (2431, 64, 640, 0), (2697, 128, 1152, 1)])
+def test_small_narrowed_int8_calls_run_whole(rec, M, N, K, bt):
+    """Calls of 4-6 us whose int32 form splits K for the price of adding into C: the kernel that
+    sums a narrowed call's slices would cost them half as much again."""
+    for name in ("gemm_i8_i8", "gemm_i8_i16"):
+        rc, x = rec.call(name, M, N, K, bt)
+        assert rc == b.GEMM_OK and x["split_k"] == 1, x
 
 
 LIMIT = (16 << 20) - (64 << 10)
