@@ -248,6 +248,18 @@ bool neighbour_plan(const Problem &p, int32_t *config, int32_t *split, int32_t *
     return true;
 }
 
+// Longest rows of K (bytes) at which a GENERIC tile competes with the vectorised ones.  With a
+// column-major B the 64 x 64 one stops at 256: 400 calls of up to 2 KiB run 0.92 of its time on
+// the narrow ring tiles and the three-stage one (at 256 alike; row-major calls 0.9-0.96 of the
+// time on the GENERIC tile, at any such length).  The 32 x 128 one stops at 128: 100 calls past
+// it 0.93, mostly on the ring tile of its shape.
+static int64_t generic_row_bytes(int32_t cfg, int32_t trans_b) {
+    if (kConfigs[cfg].bm > 64) return 0;
+    if (kConfigs[cfg].bn == 128 && kConfigs[cfg].bm == 32) return 128;
+    if (kConfigs[cfg].bn == 64 && trans_b) return 256;
+    return 2048;
+}
+
 bool fits_fixed_scratch(const Plan &pl) {
     const int64_t counters = pl.split_k > 1 && pl.reduce_in_kernel == REDUCE_LAST_SLICE ? pl.tiles_m * pl.tiles_n : 0;
     return pl.workspace_bytes <= kStaticScratchBytes - kScratchCounterBytes && counters * 4 <= kScratchCounterBytes;
@@ -270,11 +282,11 @@ bool select_plan(const Problem &p, Plan *out, int32_t forced_family, int32_t for
         if (forced_family >= 0 && kConfigs[cfg].family != forced_family) continue;
         if (!config_applicable(p, cfg)) continue;
         if (forced_family < 0 && forced_config < 0 && cfg == kPingPongRowOnly) continue;   // 44 is the same kernel
-        // Where vectorised kernels can run, GENERIC ones compete only for short K (rows of at
-        // most 2 KiB), where a tile is mostly prologue and C stores and their small tiles (64
-        // rows at most, up to four to a CU) win: bf16 25440 x 64 x 64 8.6 -> 4.6 us, int8 43840 x 64 x 128 9.2 -> 5.0 us.
-        if (forced_family < 0 && forced_config < 0 && kConfigs[cfg].family == FAM_GENERIC &&
-            (p.K * elem_bytes(p.dtype) > 2048 || kConfigs[cfg].bm > 64) && vector_loads_ok(p))
+        // Where vectorised kernels can run, GENERIC ones compete only for short K, where a tile is
+        // mostly prologue and C stores and their small tiles (64 rows at most, up to four to a CU)
+        // win: bf16 25440 x 64 x 64 8.6 -> 4.6 us, int8 43840 x 64 x 128 9.2 -> 5.0 us.
+        if (forced_family < 0 && forced_config < 0 && kConfigs[cfg].family == FAM_GENERIC && vector_loads_ok(p) &&
+            p.K * elem_bytes(p.dtype) > generic_row_bytes(cfg, p.trans_b))
             continue;
         // The three-stage 64 x 64 kernel is for tiles more than half full: at M = 6 (bf16
         // 6 x 12288 x 6592, B row-major) it took 43 us against 33 of a 32-row tile, at M = 50

@@ -398,3 +398,17 @@ def test_one_row_with_few_columns_is_no_gemv(dtype):
             assert plan(dtype, 1, N, K)["kernel"] != b.GEMM_KERNEL_GEMV, (N, K)
     if dtype == I8:
         assert plan(dtype, 1, 14336, 8192)["kernel"] == b.GEMM_KERNEL_GEMV
+
+
+@pytest.mark.parametrize("dtype", [I8, BF])
+def test_generic_tiles_compete_for_short_rows_only(dtype):
+    """Aligned calls: the any-alignment tiles that other kernels beat past 256 bytes of K (64 x 64,
+    column-major B) and past 128 (32 x 128) are not chosen there; short rows still take them."""
+    e = ESZ[dtype]
+    for M in (3, 9, 40, 138, 335, 1348):
+        for N in (64, 256, 1408, 4480, 13312):
+            for kb in (384, 640, 1024, 2048):
+                assert plan_bt(dtype, M, N, kb // e)["config"] not in (0, 41), (M, N, kb)
+                assert plan(dtype, M, N, kb // e)["config"] != 41, (M, N, kb)
+    assert plan(dtype, 25440, 64, 128 // e)["config"] in (0, 42)
+    assert plan_bt(dtype, 25440, 64, 128 // e)["config"] in (0, 42)
