@@ -125,7 +125,8 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
         red_us = mode == REDUCE_LAST_SLICE ? in_kernel_us
                : mode == REDUCE_ATOMIC_FLAG ? chip.flag_us
                : element ? chip.element_launch_us
-               : mode == REDUCE_ATOMIC ? chip.fill_us : chip.separate_us;
+               : mode == REDUCE_ATOMIC ? chip.fill_us
+               : chip.separate_us + chip.separate_slice_us * double(std::max(0, pl.split_k - 12));
     }
     const bool partial_planes =
         pl.split_k > 1 && pl.reduce_in_kernel != REDUCE_ATOMIC && pl.reduce_in_kernel != REDUCE_ATOMIC_FLAG;

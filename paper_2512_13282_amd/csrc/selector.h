@@ -43,6 +43,7 @@ struct Chip {
                                           // in flight over the latency)
     double  base_us = 0.367;              // of every plan
     double  separate_us = 3.61;           // split-K: the separate reduction's launch ...
+    double  separate_slice_us = 0.25;     // ... each slice past 12 (its kernel: 4.5 us to 12, 7.7 at 24, 18 at 64),
     double  fill_us = 2.89;               // ... the fill kernel's ahead of atomic adds ...
     double  flag_us = 0.4;                // ... and waiting for the first slice's zeros
     double  last_slice_below_us = 5.0;    // largest estimate that the last slice's own sum is taken at

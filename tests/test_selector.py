@@ -412,3 +412,11 @@ def test_generic_tiles_compete_for_short_rows_only(dtype):
                 assert plan(dtype, M, N, kb // e)["config"] != 41, (M, N, kb)
     assert plan(dtype, 25440, 64, 128 // e)["config"] in (0, 42)
     assert plan_bt(dtype, 25440, 64, 128 // e)["config"] in (0, 42)
+
+
+@pytest.mark.parametrize("M,N,K,bt", [(15, 128, 14016, 0), (18, 64, 768, 1), (846, 16, 768, 1), (16, 256, 16384, 0)])
+def test_many_slices_cost_the_separate_sum(M, N, K, bt):
+    """The separate reduction's kernel takes 4.5 us up to 12 slices, 7.7 at 24 and 10.3 at 32: small
+    outputs are not cut finer than their product gains."""
+    p = plan_bt(BF, M, N, K) if bt else plan(BF, M, N, K)
+    assert p["split_k"] <= 16, p
