@@ -327,10 +327,10 @@ __device__ __forceinline__ void store4(O *dst, const O (&c)[4]) {
 // The epilogue is a template argument so that the loop bodies stay small enough to
 // unroll fully: the accumulators are then only indexed by constants and stay in
 // registers (with a run-time choice per element, the 256-register tiles of the
-// 4-wave 256 x 256 int8 kernels went to scratch).  The stores are non-temporal: C
-// is written once and not read back by the kernel, and streaming it past the caches
-// keeps the A and B panels that other workgroups are still reading resident in L2
-// and in the last-level cache (measured at 8192^3: 6 % faster for int8, 3 % for
+// 4-wave 256 x 256 int8 kernels went to scratch).  NT: the stores stream past the
+// caches (store_c_direct says when): C is written once and not read back by the
+// kernel, and the A and B panels that other workgroups are still reading stay resident
+// in L2 and in the last-level cache (measured at 8192^3: 6 % faster for int8, 3 % for
 // bf16).
 template <int DT, int EPI, bool NT, int CS, int TM, int TN>
 __device__ __forceinline__ void store_c_wide(const KernelArgs &args,
@@ -382,9 +382,10 @@ __device__ __forceinline__ void store_c_wide(const KernelArgs &args,
 }
 
 // The same, one output per store: lane l writes its registers as they are (column
-// c0 + l % 32 + 32 j, two rows per store instruction).  Kept for the 4-wave
-// 256 x 256 tiles, whose waves each hold a 128 x 128 block (256 accumulator
-// registers): the transposes' extra live values would push them into scratch.
+// c0 + l % 32 + 32 j, two rows per store instruction).  For 32-bit outputs of eight-wave
+// tiles and all outputs of the 4-wave 256 x 256 tiles, whose waves each hold a 128 x 128
+// block (256 accumulator registers): the transposes' extra live values would push those
+// into scratch.
 template <int DT, int EPI, bool NT, int CS, int TM, int TN>
 __device__ __forceinline__ void store_c_elementwise(const KernelArgs &args,
                                                     const typename Types<DT>::acc_vec (&acc)[TM][TN],
@@ -411,11 +412,13 @@ __device__ __forceinline__ void store_c_elementwise(const KernelArgs &args,
     }
 }
 
-// Which form a tile uses, as measured (same-process A/B against element-wise
-// stores): four-wave tiles of at most 64 x 64 per wave write a quarter of the
-// store instructions and gain (128 x 128 at 2048^3: 3.5 %); tiles of eight waves
-// lose 1-7 %, their epilogue being bound by the chip's aggregate write rate rather
-// than by store instructions, so the transposes only add VALU work.
+// Which form a tile uses, as measured (same-process A/B against element-wise stores).
+// 32-bit outputs: four-wave tiles of at most 64 x 64 per wave write a quarter of the
+// store instructions and gain (128 x 128 at 2048^3: 3.5 %); tiles of eight waves lose
+// 1-7 %, their epilogue being bound by the chip's aggregate write rate rather than by
+// store instructions, so the transposes only add VALU work.  Narrowed outputs write a half
+// or a quarter of the bytes in as many instructions, which then bound the eight-wave tiles
+// too: four per store wherever a wave holds at most eight fragments.
 //
 // Non-temporal stores only where every row of C starts on a 128-byte line: elsewhere a
 // fragment's piece of a row ends inside lines that the next fragment, wave or tile

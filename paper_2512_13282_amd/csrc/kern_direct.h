@@ -522,9 +522,10 @@ void gemm_lds_kernel(KernelArgs args) {
 // Stages past the end of K load zeros through an empty resource, so that every phase
 // issues the same two loads and the wait is a fixed count (12: six phases' loads).
 //
-// Measured against gemm_lds_kernel at the same tile: 8192^3 bf16 835 -> 771 us (1426
-// TFLOP/s), column-major B 845 -> 779; int8 437 -> 421 us (2610 TOPS), column-major 429
-// -> 415.  What bounds it now: MFMAs at the clock the power limit leaves (1.5-1.65 GHz).
+// Measured against gemm_lds_kernel at the same tile: 8192^3 bf16 847 -> 787 us (1397
+// TFLOP/s), column-major B 838 -> 787; int8 466 -> 439 us (2505 TOPS), column-major 459
+// -> 438 (medians of the tracked traces; a cooler card runs them in 771 and 421).  What bounds
+// it now: MFMAs, busy 85 and 77 % at the clock the power limit leaves (1.5-1.65 GHz).
 // ---------------------------------------------------------------------------
 template <int DT, bool BT>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))

@@ -176,9 +176,9 @@ void gemm_element_kernel(KernelArgs args) {
 // (94 with one stage in flight; int8 6314 x 932 x 2271 41 -> 35 us by the second);
 // bf16 2047 x 2051 x 2049, column-major B, 350 -> 47 us; int8 50176 x 64 x 147 28.1 -> 6.7 us
 // (kernel time; 8.5 with the host's launch).  The load path bounds it: each misaligned
-// 128-byte row piece touches two lines, so a 256 x 128 tile's stage takes about 2400 clocks
-// of loads beside 1024 of MFMAs.  A 256 x 256 tile over eight waves went to scratch (100-188
-// bytes a lane) and was nowhere clearly faster.
+// 128-byte row piece touches two lines, and a 256 x 128 tile's stage takes about 2900 clocks
+// beside 1024 of MFMAs (counters of the first call: address units busy 63 % of the time,
+// matrix cores 35 %).  A 256 x 256 tile over eight waves goes to scratch.
 // ---------------------------------------------------------------------------
 typedef unsigned u32x4_any_t __attribute__((ext_vector_type(4), aligned(1)));
 
