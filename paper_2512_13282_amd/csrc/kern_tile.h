@@ -4,6 +4,7 @@
 #pragma once
 
 #include "gemm_common.h"
+#include "pieces.h"
 
 namespace gemm {
 
@@ -242,8 +243,7 @@ void gemm_tile_kernel(KernelArgs args) {
     uint32_t a_voff[A_CH];
 #pragma unroll
     for (int i = 0; i < A_CH; ++i) {
-        const int row = a_row + i * A_STEP;
-        a_voff[i] = uint32_t((row < a_last ? row : a_last) * lda_b) + uint32_t(a_c * 16);
+        a_voff[i] = uint32_t(row_piece(a_row + i * A_STEP, a_last, lda_b, a_c));
     }
     // B: column-major as A over the tile's rows (n); row-major: row b_row + i * B_STEP (k),
     // columns from b_col (pieces wholly past N take the row's last column on).
@@ -254,8 +254,8 @@ void gemm_tile_kernel(KernelArgs args) {
 #pragma unroll
     for (int i = 0; i < B_CH; ++i) {
         const int row = b_row + i * B_STEP;
-        b_voff[i] = BT ? uint32_t((row < b_last ? row : b_last) * ldb_b) + uint32_t(b_c * 16)
-                       : uint32_t(row * ldb_b) + uint32_t((b_col < N ? b_col : N - 1) * E);
+        b_voff[i] = BT ? uint32_t(row_piece(row, b_last, ldb_b, b_c))
+                       : uint32_t(row * ldb_b) + uint32_t(col_piece(b_col, N) * E);
     }
     const uint8_t *const a_base = static_cast<const uint8_t *>(args.A) + (m0 * args.lda + k_begin) * E;
     const uint8_t *const b_base =
@@ -284,7 +284,7 @@ void gemm_tile_kernel(KernelArgs args) {
         } else {
             const int rem = int(k_end - k_begin - int64_t(kt) * BK);          // 1 .. BK
             // K-contiguous rows: bytes past the row's end (offset from this stage's start)
-            auto back = [&](int c) { const int over = c * 16 + 16 - rem * E; return over > 0 ? over : 0; };
+            auto back = [&](int c) { return row_piece_back(c, rem * E); };
 #pragma unroll
             for (int i = 0; i < A_CH; ++i)
                 ra[i] = shift_down(*reinterpret_cast<const u32x4_any_t *>(ap + int64_t(a_voff[i]) - back(a_c)), back(a_c));
@@ -295,9 +295,9 @@ void gemm_tile_kernel(KernelArgs args) {
                                        back(b_c));
                 } else {
                     const int row = b_row + i * B_STEP;
-                    const int64_t col = b_col + VECE <= N ? b_col : N - VECE;
+                    const int64_t col = col_piece_tail(b_col, N, VECE);
                     const u32x4_t v = shift_down(
-                        load_any16(bp + (row < rem ? row : rem - 1) * ldb_b, uint32_t(col * E)), int(b_col - col) * E);
+                        load_any16(bp + row_tail(row, rem) * ldb_b, uint32_t(col * E)), int(b_col - col) * E);
                     rb[i] = row < rem ? v : u32x4_t{0u, 0u, 0u, 0u};
                 }
             }
