@@ -218,9 +218,10 @@ __device__ __forceinline__ int32_t requant_nearest_even(int32_t v, int shift, in
 }
 
 // fp32 -> bf16, round to nearest with ties to even: the hardware conversion
-// (v_cvt_pk_bf16_f32).  Over all 2^32 inputs it gives the bits of the integer form it
-// replaced: a NaN keeps its sign and upper half with the quiet bit set, subnormals are
-// kept, and a finite value past the largest bf16 lands on the infinity.
+// (v_cvt_pk_bf16_f32).  A NaN keeps its sign and upper half with the quiet bit set,
+// subnormals are kept, and a finite value past the largest bf16 lands on the infinity
+// (compared once over all 2^32 inputs with the integer form it replaced; the tests take
+// sums of any bits from 2^-90 up, ties and the overflow).
 __device__ __forceinline__ uint16_t bf16_nearest_even(float f) {
     return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f));
 }

@@ -232,3 +232,31 @@ def test_bf16_output_rounds_the_fp32_calls_result(M, N, K, bt):
     Bx = np.ascontiguousarray(B.T) if bt else B
     wide = g.gemm_gpu_bt(BF, A, Bx) if bt else g.gemm_gpu(BF, A, Bx)
     assert np.array_equal(run_epilogue("bf16", A, Bx, bt=bool(bt)), inputs.bf16_bits_from_f32(wide))
+
+
+@pytest.mark.parametrize("cfg", [0, 10, 20])
+def test_bf16_rounding_of_any_sum(cfg):
+    """fp32 sums of any bits and magnitude (2^-90 up, past the largest bf16 too), half of them at
+    and beside the ties: each is three bf16 parts of eight bits, whose sum is exact in any order."""
+    rng = np.random.default_rng(61)
+    M, N, K = 1 << 16, 64, 8
+    u = rng.integers(0, 1 << 32, M, dtype=np.uint64).astype(np.uint32)
+    exp = rng.integers(127 - 90, 255, M).astype(np.uint32)              # no NaN or infinity
+    u = (u & np.uint32(0x807FFFFF)) | (exp << np.uint32(23))
+    near = np.array([0x7FFF, 0x8000, 0x8001, 0xFFFF, 0], np.uint32)
+    u[::2] = (u[::2] & np.uint32(0xFFFF0000)) | near[rng.integers(0, 5, M // 2)]
+    u[:8] = [0x7F7FFFFF, 0xFF7FFFFF, 0x7F7F8000, 0xFF7F8000, 0x7F7F7FFF, 0xFF7F7FFF, 0x3F808000, 0x3F818000]
+    v = u.view(np.float32)
+    top = lambda x: (x.view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32)
+    hi = top(v)
+    mid = top(v - hi)
+    lo = v - hi - mid
+    A = np.zeros((M, K), np.uint16)
+    for k, part in enumerate((hi, mid, lo)):
+        assert np.array_equal(top(part), part)                          # each part is a bf16
+        A[:, k] = part.view(np.uint32) >> np.uint32(16)
+    B = np.full((K, N), 0x3F80, np.uint16)                              # ones
+    g.force(BF, b.GEMM_KERNEL_AUTO, cfg, 1)
+    C = run_epilogue("bf16", A, B)
+    ref = inputs.bf16_bits_from_f32(v)
+    assert np.array_equal(C, np.broadcast_to(ref[:, None], (M, N))), "bf16 rounding differs"
