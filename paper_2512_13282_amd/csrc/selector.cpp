@@ -181,12 +181,15 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
     // cannot reach the HBM rate (measured: 112 unsplit workgroups of 32 x 128 at M = 16
     // take 1.4x the time of 224 split ones).
     // The row-major GEMV walks its rows one after another whatever their width: columns past N
-    // save it nothing (1 x 64 x 11264 int8 in eight slices 40 us, a 32-row ring tile 7.2).
+    // save it nothing (1 x 64 x 11264 int8 in eight slices 40 us, a 32-row ring tile 7.2).  It
+    // streams at 18 GB/s, its launch included (at the tiles' rate in its price, 150 int8 calls
+    // that it was chosen for ran 1.17 times the ring tiles' time).
     if (pl.tiles_m == 1 && p.K > 0) {
         const int64_t cols = c.family == FAM_GEMV ? c.bn : std::min<int64_t>(c.bn, p.N);
         const double wg_bytes = double(std::min<int64_t>(pl.k_chunk, p.K)) *
                                 (double(std::min<int64_t>(c.bm, p.M)) + double(cols) * b_line) * e;
-        pl.t_mem_us = std::max(pl.t_mem_us, double(rounds) * wg_bytes / chip.wg_cold_bytes_per_s * 1e6);
+        const double rate = c.family == FAM_GEMV && !p.trans_b ? chip.gemv_bytes_per_s : chip.wg_cold_bytes_per_s;
+        pl.t_mem_us = std::max(pl.t_mem_us, double(rounds) * wg_bytes / rate * 1e6);
     }
 
     pl.t_total_us = std::max(pl.t_comp_us, pl.t_mem_us) + overhead_us + (element ? chip.element_launch_us : chip.base_us) + red_us;

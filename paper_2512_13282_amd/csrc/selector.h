@@ -41,6 +41,7 @@ struct Chip {
     double  reread_bytes_per_s = 19.8e12;   // A/B tile re-reads mostly served by L2/MALL
     double  wg_cold_bytes_per_s = 31.2e9;  // one workgroup streaming its own strip of B (its loads
                                           // in flight over the latency)
+    double  gemv_bytes_per_s = 18e9;      // ... one of the row-major GEMV, its launch and first loads included
     double  base_us = 0.367;              // of every plan
     double  separate_us = 3.61;           // split-K: the separate reduction's launch ...
     double  separate_slice_us = 0.25;     // ... each slice past 12 (its kernel: 4.5 us to 12, 7.7 at 24, 18 at 64),
