@@ -421,3 +421,9 @@ def test_many_slices_cost_the_separate_sum(M, N, K, bt):
     outputs are not cut finer than their product gains."""
     p = plan_bt(BF, M, N, K) if bt else plan(BF, M, N, K)
     assert p["split_k"] <= 16, p
+
+
+def test_short_int8_products_with_a_column_major_b_run_whole():
+    """5-8 us in two slices that add into C, a quarter less whole."""
+    for M, N, K in ((385, 1344, 1184), (526, 1088, 1344), (790, 896, 1792), (1464, 288, 1168), (39, 64, 192)):
+        assert plan_bt(I8, M, N, K)["split_k"] == 1, (M, N, K)
