@@ -118,13 +118,14 @@ Plan evaluate(const Problem &p, int32_t cfg, int32_t split, const Chip &chip, in
             mode = REDUCE_SEPARATE;
         if (mode == REDUCE_ATOMIC_FLAG && c.family != FAM_RING && c.family != FAM_GEMV) mode = REDUCE_ATOMIC;
         pl.reduce_in_kernel = mode;
-        // Atomic with slice 0's zeros: what the other slices wait for beyond their own work.  At
-        // 0.1 us (and at 0.4) the model split products of a few microseconds that run faster whole:
-        // int8 80 x 256 x 256 5.6 us in two slices, 4.6 in one; 385 x 1344 x 1184, B column-major,
-        // 8.0 and 6.0.  Of 8800 sampled int8 calls 500 change plan from 0.4 to 1.0 us, to 0.92 of
-        // the time, 35 to more than 1.05.
+        // Atomic with slice 0's zeros: what the other slices wait for beyond their own work, by the
+        // rows that are zeroed.  Priced at 0.4 us for all, the model split products of a few
+        // microseconds that run faster whole (int8 80 x 256 x 256 5.6 us in two slices, 4.6 in one;
+        // 385 x 1344 x 1184, B column-major, 8.0 and 6.0); at 1 us for all it ran a few rows whole
+        // that gain by a split (1 x 2112 x 9856 10.0 us, 7.8 in two).  500 sampled int8 calls that
+        // change plan between the first and this: 0.90 of the time, 18 of them more than 1.05.
         red_us = mode == REDUCE_LAST_SLICE ? in_kernel_us
-               : mode == REDUCE_ATOMIC_FLAG ? chip.flag_us
+               : mode == REDUCE_ATOMIC_FLAG ? chip.flag_us + chip.flag_row_us * double(std::min<int64_t>(rows, 24))
                : element ? chip.element_launch_us
                : mode == REDUCE_ATOMIC ? chip.fill_us
                : chip.separate_us + chip.separate_slice_us * double(std::max(0, pl.split_k - 12));

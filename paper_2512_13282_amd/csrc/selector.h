@@ -46,7 +46,8 @@ struct Chip {
     double  separate_us = 3.61;           // split-K: the separate reduction's launch ...
     double  separate_slice_us = 0.25;     // ... each slice past 12 (its kernel: 4.5 us to 12, 7.7 at 24, 18 at 64),
     double  fill_us = 2.89;               // ... the fill kernel's ahead of atomic adds ...
-    double  flag_us = 1.0;                // ... and waiting for the first slice's zeros
+    double  flag_us = 0.5, flag_row_us = 0.03;   // ... and waiting for the first slice's zeros, by the
+                                          // tile's valid rows up to 24
     double  last_slice_below_us = 5.0;    // largest estimate that the last slice's own sum is taken at
     // The element-wise kernel: the rates of compulsory traffic and of re-reads, a round of
     // workgroups' first loads and C stores, and a launch, its own or beside it.
