@@ -258,11 +258,13 @@ bool neighbour_plan(const Problem &p, int32_t *config, int32_t *split, int32_t *
 // column-major B the 64 x 64 one stops at 256: 400 calls of up to 2 KiB run 0.92 of its time on
 // the narrow ring tiles and the three-stage one (at 256 alike; row-major calls 0.9-0.96 of the
 // time on the GENERIC tile, at any such length).  The 32 x 128 one stops at 128: 100 calls past
-// it 0.93, mostly on the ring tile of its shape.
-static int64_t generic_row_bytes(int32_t cfg, int32_t trans_b) {
-    if (kConfigs[cfg].bm > 64) return 0;
-    if (kConfigs[cfg].bn == 128 && kConfigs[cfg].bm == 32) return 128;
-    if (kConfigs[cfg].bn == 64 && trans_b) return 256;
+// it 0.93, mostly on the ring tile of its shape.  So does the 64 x 128 one until it has two
+// workgroups for every compute unit (350 calls 0.94; with more, 150 calls 1.01 without it).
+static int64_t generic_row_bytes(const Problem &p, int32_t cfg, const Chip &chip) {
+    const TileConfig &c = kConfigs[cfg];
+    if (c.bm > 64) return 0;
+    if (c.bn == 128 && (c.bm == 32 || ceil_div(p.M, c.bm) * ceil_div(p.N, c.bn) < 2 * chip.cus)) return 128;
+    if (c.bn == 64 && p.trans_b) return 256;
     return 2048;
 }
 
@@ -292,7 +294,7 @@ bool select_plan(const Problem &p, Plan *out, int32_t forced_family, int32_t for
         // mostly prologue and C stores and their small tiles (64 rows at most, up to four to a CU)
         // win: bf16 25440 x 64 x 64 8.6 -> 4.6 us, int8 43840 x 64 x 128 9.2 -> 5.0 us.
         if (forced_family < 0 && forced_config < 0 && kConfigs[cfg].family == FAM_GENERIC && vector_loads_ok(p) &&
-            p.K * elem_bytes(p.dtype) > generic_row_bytes(cfg, p.trans_b))
+            p.K * elem_bytes(p.dtype) > generic_row_bytes(p, cfg, chip))
             continue;
         // The three-stage 64 x 64 kernel is for tiles more than half full: at M = 6 (bf16
         // 6 x 12288 x 6592, B row-major) it took 43 us against 33 of a 32-row tile, at M = 50

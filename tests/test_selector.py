@@ -411,6 +411,9 @@ def test_generic_tiles_compete_for_short_rows_only(dtype):
             for kb in (384, 640, 1024, 2048):
                 assert plan_bt(dtype, M, N, kb // e)["config"] not in (0, 41), (M, N, kb)
                 assert plan(dtype, M, N, kb // e)["config"] != 41, (M, N, kb)
+                # 64 x 128: two workgroups for every compute unit, or short rows
+                p = plan(dtype, M, N, kb // e)
+                assert p["config"] != 42 or p["grid"] >= 512, (M, N, kb)
     assert plan(dtype, 25440, 64, 128 // e)["config"] in (0, 42)
     assert plan_bt(dtype, 25440, 64, 128 // e)["config"] in (0, 42)
 
