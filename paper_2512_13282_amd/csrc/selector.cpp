@@ -254,18 +254,22 @@ bool neighbour_plan(const Problem &p, int32_t *config, int32_t *split, int32_t *
     return true;
 }
 
-// Longest rows of K (bytes) at which a GENERIC tile competes with the vectorised ones.  With a
-// column-major B the 64 x 64 one stops at 256: 400 calls of up to 2 KiB run 0.92 of its time on
-// the narrow ring tiles and the three-stage one (at 256 alike; row-major calls 0.9-0.96 of the
-// time on the GENERIC tile, at any such length).  The 32 x 128 one stops at 128: 100 calls past
-// it 0.93, mostly on the ring tile of its shape.  So does the 64 x 128 one until it has two
-// workgroups for every compute unit (350 calls 0.94; with more, 150 calls 1.01 without it).
+// Longest rows of K (bytes) at which a GENERIC tile competes with the vectorised ones: a grid that
+// leaves a compute unit too few of them to hide first loads is passed by for longer rows.
+//   64 x 64, B column-major: 256 below three workgroups a compute unit (400 calls of up to 2 KiB
+//     0.92 of its time on the narrow ring tiles and the three-stage one; at 256 alike; from three
+//     on 0.96 of the others' time, 59367 x 64 x 960 14.1 us against 16.8).  Row-major calls take
+//     0.9-0.96 of the time on it at any such length.
+//   64 x 128: 128 below two workgroups a compute unit (500 calls 0.94 without it; with more, 150
+//     calls 1.01 without it).
+//   32 x 128: 128 (100 calls past it 0.93, mostly on the ring tile of its shape).
 static int64_t generic_row_bytes(const Problem &p, int32_t cfg, const Chip &chip) {
     const TileConfig &c = kConfigs[cfg];
     if (c.bm > 64) return 0;
-    if (c.bn == 128 && (c.bm == 32 || ceil_div(p.M, c.bm) * ceil_div(p.N, c.bn) < 2 * chip.cus)) return 128;
-    if (c.bn == 64 && p.trans_b) return 256;
-    return 2048;
+    if (c.bn == 128 && c.bm == 32) return 128;
+    const int64_t per_cu = c.bn == 128 ? 2 : 3;
+    if (ceil_div(p.M, c.bm) * ceil_div(p.N, c.bn) >= per_cu * chip.cus) return 2048;
+    return c.bn == 128 ? 128 : p.trans_b ? 256 : 2048;
 }
 
 bool fits_fixed_scratch(const Plan &pl) {

@@ -415,6 +415,7 @@ def test_generic_tiles_compete_for_short_rows_only(dtype):
                 p = plan(dtype, M, N, kb // e)
                 assert p["config"] != 42 or p["grid"] >= 512, (M, N, kb)
     assert plan(dtype, 25440, 64, 128 // e)["config"] in (0, 42)
+    assert plan_bt(dtype, 59392, 64, 960 // e)["config"] == 0       # 928 workgroups
     assert plan_bt(dtype, 25440, 64, 128 // e)["config"] in (0, 42)
 
 
