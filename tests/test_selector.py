@@ -431,3 +431,11 @@ def test_short_int8_products_with_a_column_major_b_run_whole():
     """5-8 us in two slices that add into C, a quarter less whole."""
     for M, N, K in ((385, 1344, 1184), (526, 1088, 1344), (790, 896, 1792), (1464, 288, 1168), (39, 64, 192)):
         assert plan_bt(I8, M, N, K)["split_k"] == 1, (M, N, K)
+
+
+@pytest.mark.parametrize("dtype,M,N,K,bt", [(BF, 736, 768, 512, 0), (BF, 128, 640, 512, 0), (I8, 182, 1536, 1024, 0),
+                                            (I8, 912, 896, 2880, 1), (BF, 336, 640, 768, 1), (I8, 592, 704, 1024, 1)])
+def test_mid_size_products_take_the_three_stage_kernel(dtype, M, N, K, bt):
+    """5-9 us there, a fifth to a third more on the any-alignment and narrow ring tiles."""
+    p = (plan_bt if bt else plan)(dtype, M, N, K)
+    assert p["name"] == "direct_64x64_w4_s3", p
