@@ -131,7 +131,7 @@ def test_noalloc_runs_the_best_plan_that_fits(rec):
     assert changed >= 5
 
 
-@pytest.mark.parametrize("M,N,K", [(1504, 1408, 2880), (196, 2833, 7273), (330, 2555, 9583), (1200, 1792, 3136),
+@pytest.mark.parametrize("M,N,K", [(1520, 1856, 6976), (196, 2833, 7273), (330, 2555, 9583), (1200, 1792, 3136),
                                    (512, 8192, 8192), (2048, 4096, 14336), (256, 13824, 5120)])
 def test_noalloc_fallback_fills_the_chip(rec, M, N, K):
     """Calls whose split plan does not fit: 23 to 128 workgroups if that plan's tile ran

@@ -439,3 +439,13 @@ def test_mid_size_products_take_the_three_stage_kernel(dtype, M, N, K, bt):
     """5-9 us there, a fifth to a third more on the any-alignment and narrow ring tiles."""
     p = (plan_bt if bt else plan)(dtype, M, N, K)
     assert p["name"] == "direct_64x64_w4_s3", p
+
+
+@pytest.mark.parametrize("dtype,M,N,K,bt,slower", [(BF, 14976, 384, 12544, 0, (40, 1)), (BF, 6240, 448, 12736, 1, (40, 2)),
+                                                   (I8, 552, 28416, 6080, 1, (40, 1)), (BF, 279, 7872, 11712, 1, (40, 2)),
+                                                   (BF, 1278, 1664, 3008, 0, (40, 2))])
+def test_alike_compute_and_memory_times_add_up(dtype, M, N, K, bt, slower):
+    """With several tile rows a plan whose compute and memory times are alike takes longer than
+    either: these calls run 0.66-0.78 of the time on other plans than the one named."""
+    p = (plan_bt if bt else plan)(dtype, M, N, K)
+    assert (p["config"], p["split_k"]) != slower, p
